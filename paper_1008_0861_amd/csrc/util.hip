@@ -54,22 +54,29 @@ hipError_t launch_permute(const T* in, T* out, const int n[3], const int64_t ds[
 template <typename T>
 __global__ void __launch_bounds__(256) reduce_kernel(const T* __restrict__ x, int64_t N, ReduceParams R) {
     // partials only; a later launch folds them
-    double s = 0.0, mn = __builtin_huge_val(), mx = -__builtin_huge_val();
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const double v = (double)x[i];
-        s += v;
-        mn = fmin(mn, v);
-        mx = fmax(mx, v);
+    constexpr int U = 8;  // loads in flight per thread
+    double s4[U] = {}, mn = __builtin_huge_val(), mx = -__builtin_huge_val();
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i0 < N; i0 += U * stride) {
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[i0 + u * stride < N ? i0 + u * stride : i0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            s4[u] += i0 + u * stride < N ? (double)v[u] : 0.0;
+            mn = fmin(mn, (double)v[u]);
+            mx = fmax(mx, (double)v[u]);
+        }
     }
+    const double s = ((s4[0] + s4[1]) + (s4[2] + s4[3])) + ((s4[4] + s4[5]) + (s4[6] + s4[7]));
     block_partials(R.partials, s, mn, mx);
 }
 
-__global__ void __launch_bounds__(256) fold_kernel(FoldParams f) { fold_partials(f); }
+__global__ void __launch_bounds__(1024) fold_kernel(FoldParams f) { fold_partials(f); }
 
 hipError_t launch_fold(const FoldParams& f, hipStream_t st) {
     if (f.count < 1) return hipSuccess;
-    hipLaunchKernelGGL(fold_kernel, dim3(f.count), dim3(256), 0, st, f);
+    hipLaunchKernelGGL(fold_kernel, dim3(f.count), dim3(f.nblocks > 1024 ? 1024 : 256), 0, st, f);
     return hipGetLastError();
 }
 
