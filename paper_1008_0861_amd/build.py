@@ -29,11 +29,17 @@ FLAGS = [
 # dwords; the kernel's argument list is laid out for that).
 SOURCE_FLAGS = {"sweep.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
 
+# Sources whose kernel instantiations are shared out over several objects
+# (each compiled with -DASD_PART=i), so that they compile side by side.
+PARTS = {"batch.hip": 6, "sweep.hip": 8}
 
-def _compile(src):
+
+def _compile(unit):
+    src, part = unit
     path = os.path.join(CSRC, src)
-    obj = os.path.join(BUILD, src + ".o")
-    cmd = [HIPCC, "-x", "hip", *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", path, "-o", obj]
+    split = [] if part is None else [f"-DASD_PART={part}"]
+    obj = os.path.join(BUILD, src + ("" if part is None else f".{part}") + ".o")
+    cmd = [HIPCC, "-x", "hip", *FLAGS, *SOURCE_FLAGS.get(src, []), *split, "-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     return src, r.returncode, r.stdout + r.stderr, obj
 
@@ -41,11 +47,12 @@ def _compile(src):
 def build(verbose=False):
     """Compile every source and link libasd.so; raises on failure."""
     os.makedirs(BUILD, exist_ok=True)
-    srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    jobs = min(8, len(srcs))
+    srcs = sorted((s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))), key=lambda s: s not in PARTS)
+    units = [(s, i) for s in srcs for i in (range(PARTS[s]) if s in PARTS else [None])]
+    jobs = min(8, len(units))
     objs = []
     with ThreadPoolExecutor(jobs) as ex:
-        for src, rc, out, obj in ex.map(_compile, srcs):
+        for src, rc, out, obj in ex.map(_compile, units):
             # the host pass does not know the packed-fp32 feature: drop that warning
             msg = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip())
             if rc != 0:

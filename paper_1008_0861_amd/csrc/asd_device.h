@@ -94,14 +94,31 @@ __device__ __forceinline__ int64_t nb_coord(int64_t c, int64_t n, bool periodic)
 // for the store phase.  A few spare slots follow the n slots of a line, so
 // that a lane may read a whole MMAX-cell window past the line's end (the
 // values there are ignored).  When every segment of the line has the same
-// power-of-two length, a 16-byte pad follows every 2^pad slots, 2^pad being
-// the distance between the segments of neighbouring lanes, so that those
-// lanes hit distinct banks; no segment then contains a pad, and a segment's
+// power-of-two length (and every lane of the line has one), a 16-byte pad
+// follows every 2^pad slots, 2^pad being the distance between the segments
+// of neighbouring lanes, so that those lanes hit distinct banks; no segment then contains a pad, and a segment's
 // slots are always consecutive.  When several waves share a line, the
 // interface reduction exchanges through two buffers with one 4-element
 // entry per thread; on aligned tiles with segments of at least 8 cells the
 // buffers live in the segments' own face slots instead (no extra bytes).
+//
+// tw (the 4-step scheme's two solves in one launch): slots of four elements
+// [A, PHI, F, -], F the transverse part of PHI.
+//
+// lpl: lanes of a wave per line, 64, or 32 (two lines per wave).
 __host__ __device__ inline int slot_off(int p, int es, int pad) { return p * 2 * es + ((p >> pad) << 4); }
+__host__ __device__ inline int cell_off1(int p, int es, int pad) { return p * 4 * es + ((p >> pad) << 4); }
+__host__ __device__ inline int cell_off2(int p, int es, int pad) { return (p + (p >> pad)) * 2 * es; }
+
+// Slots per pad of an aligned tile (log2): the distance between the segments
+// of neighbouring lanes, 4 wpl segments where whole waves own a line (the
+// lane order of wave_pcr.h), one where lines share a wave.
+__host__ __device__ inline int pad_log2(int m, int wpl, int lpl) {
+    const int d = lpl < 64 ? m : 4 * m * wpl;
+    int l = 0;
+    while ((2 << l) <= d) ++l;
+    return l;
+}
 
 static constexpr int kRowSpare = 17;  // spare slots after the n face slots of a line
 
@@ -116,21 +133,15 @@ struct TileLayout {
     int rows2_at;  // cell-slot layout, 3-D: offset of the pair rows
 };
 
-__host__ __device__ inline TileLayout tile_layout(int es, int ndim, int n, int lpw, int nthreads, int wpl,
-                                                  int nseg_log2, int mmax) {
-    (void)ndim;
+__host__ __device__ inline TileLayout tile_layout(int es, int n, int lpw, int nthreads, int wpl, int nseg_log2,
+                                                  int mmax, int lpl, bool tw) {
     TileLayout L;
     L.row2 = 0;
     L.rows2_at = 0;
     const int m = n >> nseg_log2;
-    L.aligned = (m << nseg_log2) == n && m == mmax;  // mmax is a power of two
-    L.pad = 30;
-    if (L.aligned && m * wpl >= 2) {
-        int l = 0;
-        while ((2 << l) <= m * wpl) ++l;
-        L.pad = l;  // 2^pad = m * wpl: segments of neighbouring lanes
-    }
-    int r1 = (slot_off(n + kRowSpare, es, L.pad) + 15) & ~15;
+    L.aligned = (m << nseg_log2) == n && m == mmax && (1 << nseg_log2) == lpl * wpl;
+    L.pad = L.aligned && m * wpl >= 2 ? pad_log2(m, wpl, lpl) : 30;
+    int r1 = ((tw ? cell_off1(n + kRowSpare, es, L.pad) : slot_off(n + kRowSpare, es, L.pad)) + 15) & ~15;
     if (((r1 >> 4) & 1) == 0) r1 += 16;  // odd number of 16-byte units: rows start in different banks
     L.row1 = r1;
     int at = lpw * r1;
@@ -156,20 +167,12 @@ __host__ __device__ inline TileLayout tile_layout(int es, int ndim, int n, int l
 // buffers of one slot per thread; the second lives in the dead [S1, A, B1]
 // part of the line's first slots when the line has at least as many cells
 // as lanes (pcr1_at = -1).
-__host__ __device__ inline int cell_off1(int p, int es, int pad) { return p * 4 * es + ((p >> pad) << 4); }
-__host__ __device__ inline int cell_off2(int p, int es, int pad) { return (p + (p >> pad)) * 2 * es; }
-
 __host__ __device__ inline TileLayout tile_layout_cell(int es, int ndim, int n, int lpw, int nthreads, int wpl,
                                                        int nseg_log2, int mmax) {
     TileLayout L;
     const int m = n >> nseg_log2;
-    L.aligned = (m << nseg_log2) == n && m == mmax;
-    L.pad = 30;
-    if (L.aligned && m * wpl >= 2) {
-        int l = 0;
-        while ((2 << l) <= m * wpl) ++l;
-        L.pad = l;
-    }
+    L.aligned = (m << nseg_log2) == n && m == mmax && (1 << nseg_log2) == 64 * wpl;
+    L.pad = L.aligned && m * wpl >= 2 ? pad_log2(m, wpl, 64) : 30;
     int r1 = cell_off1(n + 1 + kRowSpare, es, L.pad);
     if (((r1 >> 4) & 1) == 0) r1 += 16;
     L.row1 = r1;

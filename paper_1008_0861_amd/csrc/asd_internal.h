@@ -18,8 +18,8 @@
 struct SweepCfg {
     int wpl = 1, lpw = 1, P = 2, mmax = 1, io = 1;
     int variant = asd::SWEEP_FACE_SLOTS;
-    int half = 0;  // two lines per wave (32 lanes per line; face body, batches only)
-    int nthreads() const { return (half ? 32 : 64 * wpl * io) * lpw; }
+    int lpl = 64;  // lanes of a wave per line: 64, or 32 (two lines per wave; face body, batches only)
+    int nthreads() const { return lpl * wpl * io * lpw; }
 };
 
 // gfx950: 160 KiB of LDS per workgroup; keep 2 KiB for static shared data.
@@ -39,15 +39,13 @@ inline int ilog2(int v) {
 
 // LDS layout and bytes of a sweep launch (slot rows of the lpw lines and the
 // interface-exchange buffers) for either tile body.
-inline asd::TileLayout sweep_layout(int es, int ndim, int n, int lpw, int wpl, int nthreads, int mmax, int variant,
-                                    int half = 0) {
-    const int P = half ? 32 : std::min(64 * wpl, pow2_floor(n));
-    return variant == asd::SWEEP_CELL_SLOTS ? asd::tile_layout_cell(es, ndim, n, lpw, nthreads, wpl, ilog2(P), mmax)
-                                            : asd::tile_layout(es, ndim, n, lpw, nthreads, wpl, ilog2(P), mmax);
+inline asd::TileLayout sweep_layout(int es, int ndim, int n, const SweepCfg& c, bool tw = false) {
+    return c.variant == asd::SWEEP_CELL_SLOTS
+               ? asd::tile_layout_cell(es, ndim, n, c.lpw, c.nthreads(), c.wpl, ilog2(c.P), c.mmax)
+               : asd::tile_layout(es, n, c.lpw, c.nthreads(), c.wpl, ilog2(c.P), c.mmax, c.lpl, tw);
 }
-inline size_t sweep_lds(int es, int ndim, int n, int lpw, int wpl, int nthreads, int mmax,
-                        int variant = asd::SWEEP_FACE_SLOTS, int half = 0) {
-    return (size_t)sweep_layout(es, ndim, n, lpw, wpl, nthreads, mmax, variant, half).total;
+inline size_t sweep_lds(int es, int ndim, int n, const SweepCfg& c, bool tw = false) {
+    return (size_t)sweep_layout(es, ndim, n, c, tw).total;
 }
 
 inline int sweep_threads_cap(int es, int mmax, int variant = asd::SWEEP_FACE_SLOTS) {
@@ -97,18 +95,30 @@ inline bool choose_sweep_cfg_wpl(int es, int ndim, int n, bool chi, int wpl, int
     const int cap = sweep_threads_cap(es, mmax, variant);
     const int tpl = 64 * wpl * io;  // threads per line
     if (tpl > cap) return false;
-    int lpw = want_lpw;
-    if (lpw <= 0) lpw = std::max(1, 256 / (64 * wpl));
-    while (lpw > 1 && (tpl * lpw > cap || sweep_lds(es, ndim, n, lpw, wpl, tpl * lpw, mmax, variant) > kLdsLimit))
-        lpw /= 2;
-    if (tpl * lpw > cap) return false;
-    if (sweep_lds(es, ndim, n, lpw, wpl, tpl * lpw, mmax, variant) > kLdsLimit) return false;
-    out->wpl = wpl;
-    out->lpw = lpw;
-    out->P = P;
-    out->mmax = mmax;
-    out->io = io;
-    out->variant = variant;
+    SweepCfg c;
+    c.wpl = wpl;
+    c.P = P;
+    c.mmax = mmax;
+    c.io = io;
+    c.variant = variant;
+    c.lpw = want_lpw > 0 ? want_lpw : std::max(1, 256 / (64 * wpl));
+    while (c.lpw > 1 && (tpl * c.lpw > cap || sweep_lds(es, ndim, n, c) > kLdsLimit)) c.lpw /= 2;
+    if (tpl * c.lpw > cap) return false;
+    if (sweep_lds(es, ndim, n, c) > kLdsLimit) return false;
+    *out = c;
+    return true;
+}
+
+// The launch shape of the two-solve launches (SWEEP_TWICE) for shape c:
+// the face body with as many lines per workgroup as its LDS slots (twice as
+// large) and its register budget allow.  False: it does not fit.
+inline bool twice_cfg(int es, int ndim, int n, SweepCfg c, SweepCfg* out) {
+    c.variant = asd::SWEEP_FACE_SLOTS;
+    c.io = 1;
+    const int cap = asd::sweep_twice_max_threads(es, c.mmax);
+    while (c.lpw > 1 && (c.nthreads() > cap || sweep_lds(es, ndim, n, c, true) > kLdsLimit)) c.lpw /= 2;
+    if (c.nthreads() > cap || sweep_lds(es, ndim, n, c, true) > kLdsLimit) return false;
+    *out = c;
     return true;
 }
 
@@ -185,11 +195,16 @@ enum : int {
     SWEEP_KEEP_LAYOUT = 2,  // output in the input layout
     SWEEP_SOURCE = 4,       // dt Q joins the right-hand side (input in the natural layout)
     SWEEP_REDUCE_INPUT = 8, // the reduction (red) sums the input state instead of the output
+    SWEEP_TWICE = 16,       // the 4-step scheme's two solves of a direction in one launch
 };
 
 template <typename T>
 int fill_sweep_params(asd_grid g, int d, const void* in, void* out, int rhs_mode, const SweepCfg& c,
                       asd::SweepParams<T>* P);
+// Whether a 4-step grid runs its two solves per direction in one launch:
+// the coefficients are those of the step (not chi(T), whose second solve has
+// its own) and the larger tile fits on every axis.
+bool four_step_twice(asd_grid g, const SweepCfg* cfg);
 int check_fields(asd_grid g, bool need_T);
 int prepare(asd_grid g, double dt);  // dt > 0: face coefficients for dt
 int64_t layout_stride(const asd_grid g, int L, int a);

@@ -117,9 +117,15 @@ template <typename T, int MMAX>
 struct SweepCellBounds {
     static constexpr int max_threads = sweep_cell_max_threads((int)sizeof(T), MMAX);
 };
+// The 4-step scheme's two solves in one launch hold six arrays of MMAX
+// values more per lane than one solve does in its last phase.
+__host__ __device__ constexpr int sweep_twice_max_threads(int es, int mmax) {
+    return es == 4 && mmax >= 16 ? 512 : (es == 8 && mmax >= 4 ? 256 : sweep_max_threads(es, mmax));
+}
+// twice: the 4-step scheme's two solves (face body only)
 template <typename T>
 hipError_t launch_sweep(const SweepParams<T>& P, int ndim, int mmax, dim3 grid, dim3 block,
-                        size_t lds, hipStream_t st, int variant);
+                        size_t lds, hipStream_t st, int variant, bool twice);
 hipError_t sweep_set_lds_limits(int bytes);
 
 // ---------------------------------------------------------------- explicit
@@ -291,13 +297,13 @@ __device__ __forceinline__ void fold_slot(const double* part, int nblocks, doubl
             tmx = fmax(tmx, v[u][2]);
         }
     }
+    double ts = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     ts = wave_sum_lane63(ts);
     tmn = wave_min_lane63<double>(tmn);
     tmx = wave_max_lane63<double>(tmx);
     if (lane == 63) { fs[wid] = ts; fmn[wid] = tmn; fmx[wid] = tmx; }
     __syncthreads();
     S = 0.0;
-    double ts = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     MN = fmn[0];
     MX = fmx[0];
     if (threadIdx.x == 0) {

@@ -66,13 +66,13 @@ __device__ __forceinline__ void block_reduce3(double s, M mn, M mx, double& S, d
 
 // One line tile of a batch problem on either tile body (CELL: the
 // cell-slot body of sweep_cell.h).  Both end with a block barrier.
-template <typename T, int MMAX, int LIMC, bool EXT, bool CELL, bool REUSE, bool HALF = false>
+template <typename T, int MMAX, int LIMC, bool EXT, bool CELL, bool REUSE, int LPL = 64>
 __device__ __forceinline__ void batch_tile(const SweepParams<T>& P, int l1_0, unsigned char* smem, double& lsum,
                                            T& lmin, T& lmax) {
     if constexpr (CELL)
         cell::sweep_tile<T, 2, MMAX, LIMC, EXT>(P, l1_0, 0, smem, lsum, lmin, lmax);
     else
-        sweep_tile<T, 2, MMAX, LIMC, EXT, REUSE, HALF>(P, l1_0, 0, smem, lsum, lmin, lmax);
+        sweep_tile<T, 2, MMAX, LIMC, EXT, REUSE, LPL>(P, l1_0, 0, smem, lsum, lmin, lmax);
 }
 // The tile at the problem's own capacity mm (MMAX, MMAX / 2, or 4 in the
 // capacity-16 kernels) and line packing (half: two lines per wave,
@@ -83,7 +83,7 @@ __device__ __forceinline__ void batch_tile_cap(int mm, int half, const SweepPara
                                                unsigned char* smem, double& lsum, T& lmin, T& lmax) {
     if constexpr (MMAX == 16 && !CELL) {
         if (half) {
-            batch_tile<T, MMAX, LIMC, EXT, CELL, REUSE, true>(P, l1_0, smem, lsum, lmin, lmax);
+            batch_tile<T, MMAX, LIMC, EXT, CELL, REUSE, 32>(P, l1_0, smem, lsum, lmin, lmax);
             return;
         }
     }
@@ -256,20 +256,10 @@ static hipError_t set_batch_attrs_lim(int bytes) {
     return hipSuccess;
 }
 template <typename T, int MMAX>
-static hipError_t set_batch_attrs(int bytes) {
+hipError_t set_batch_attrs(int bytes) {
     hipError_t e = set_batch_attrs_lim<T, MMAX, LIM_VANLEER, false>(bytes);
     if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, -1, false>(bytes);
     if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, -1, true>(bytes);
-    return e;
-}
-
-hipError_t batch_set_lds_limits(int bytes) {
-    hipError_t e = set_batch_attrs<float, 4>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<float, 8>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<float, 16>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 4>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 8>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 16>(bytes);
     return e;
 }
 
@@ -291,6 +281,49 @@ hipError_t batch_set_lds_limits(int bytes) {
         else ASD_BATCH_LAUNCH_BODY(KERNEL, MM, false, __VA_ARGS__);                         \
     } while (0)
 
+template <typename T, int MMAX>
+hipError_t launch_persistent_cap(const BatchProblem<T>* probs, const int* off, const int* list, int nwg, int nsteps,
+                                 int nthreads, size_t lds, int limiter, int dirichlet, int variant, const BatchOut& out,
+                                 hipStream_t st) {
+    ASD_BATCH_LAUNCH(batch_persistent_kernel, MMAX, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out);
+    return hipGetLastError();
+}
+template <typename T, int MMAX>
+hipError_t launch_grouped_cap(const BatchProblem<T>* probs, const int* group_start, int nprob, int ngroups, int d,
+                              int nthreads, size_t lds, int limiter, int dirichlet, int variant, double* partials,
+                              hipStream_t st) {
+    ASD_BATCH_LAUNCH(batch_grouped_kernel, MMAX, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials);
+    return hipGetLastError();
+}
+#undef ASD_BATCH_LAUNCH
+#undef ASD_BATCH_LAUNCH_BODY
+
+// One object per (type, capacity) compiles its kernels; the first also
+// holds the entry points that choose between them.
+#define ASD_BATCH_CAP_INST(PRE, T, MM)                                                                              \
+    PRE template hipError_t launch_persistent_cap<T, MM>(const BatchProblem<T>*, const int*, const int*, int, int,  \
+                                                         int, size_t, int, int, int, const BatchOut&, hipStream_t); \
+    PRE template hipError_t launch_grouped_cap<T, MM>(const BatchProblem<T>*, const int*, int, int, int, int,       \
+                                                      size_t, int, int, int, double*, hipStream_t);                 \
+    PRE template hipError_t set_batch_attrs<T, MM>(int);
+#if ASD_PART == 0
+ASD_BATCH_CAP_INST(, float, 4)
+ASD_BATCH_CAP_INST(extern, float, 8)
+ASD_BATCH_CAP_INST(extern, float, 16)
+ASD_BATCH_CAP_INST(extern, double, 4)
+ASD_BATCH_CAP_INST(extern, double, 8)
+ASD_BATCH_CAP_INST(extern, double, 16)
+
+hipError_t batch_set_lds_limits(int bytes) {
+    hipError_t e = set_batch_attrs<float, 4>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<float, 8>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<float, 16>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<double, 4>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<double, 8>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<double, 16>(bytes);
+    return e;
+}
+
 template <typename T>
 hipError_t launch_batch_persistent(const BatchProblem<T>* probs, const int* off, const int* list, int nwg, int nsteps,
                                    int mmax, int nthreads, size_t lds, int limiter, int dirichlet, int variant,
@@ -300,12 +333,11 @@ hipError_t launch_batch_persistent(const BatchProblem<T>* probs, const int* off,
                                                 : sweep_max_threads((int)sizeof(T), mmax)))
         return hipErrorInvalidValue;
     switch (mmax) {
-        case 4: ASD_BATCH_LAUNCH(batch_persistent_kernel, 4, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out); break;
-        case 8: ASD_BATCH_LAUNCH(batch_persistent_kernel, 8, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out); break;
-        case 16: ASD_BATCH_LAUNCH(batch_persistent_kernel, 16, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out); break;
+        case 4: return launch_persistent_cap<T, 4>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
+        case 8: return launch_persistent_cap<T, 8>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
+        case 16: return launch_persistent_cap<T, 16>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <typename T>
@@ -317,16 +349,12 @@ hipError_t launch_batch_grouped(const BatchProblem<T>* probs, const int* group_s
                                                 : sweep_max_threads((int)sizeof(T), mmax)))
         return hipErrorInvalidValue;
     switch (mmax) {
-        case 4: ASD_BATCH_LAUNCH(batch_grouped_kernel, 4, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials); break;
-        case 8: ASD_BATCH_LAUNCH(batch_grouped_kernel, 8, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials); break;
-        case 16: ASD_BATCH_LAUNCH(batch_grouped_kernel, 16, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials); break;
+        case 4: return launch_grouped_cap<T, 4>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
+        case 8: return launch_grouped_cap<T, 8>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
+        case 16: return launch_grouped_cap<T, 16>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
-#undef ASD_BATCH_LAUNCH
-#undef ASD_BATCH_LAUNCH_BODY
-
 template <typename T>
 hipError_t launch_batch_reduce0(const BatchProblem<T>* probs, int nprob, const BatchOut& out, hipStream_t st) {
     hipLaunchKernelGGL(batch_reduce0_kernel<T>, dim3(nprob), dim3(1024), 0, st, probs, out);
@@ -349,5 +377,16 @@ hipError_t launch_batch_fold(const BatchProblem<T>* probs, int nprob, const Batc
 ASD_BATCH_INST(float)
 ASD_BATCH_INST(double)
 #undef ASD_BATCH_INST
+#elif ASD_PART == 1
+ASD_BATCH_CAP_INST(, float, 8)
+#elif ASD_PART == 2
+ASD_BATCH_CAP_INST(, float, 16)
+#elif ASD_PART == 3
+ASD_BATCH_CAP_INST(, double, 4)
+#elif ASD_PART == 4
+ASD_BATCH_CAP_INST(, double, 8)
+#else
+ASD_BATCH_CAP_INST(, double, 16)
+#endif
 
 }  // namespace asd

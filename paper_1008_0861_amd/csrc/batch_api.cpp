@@ -121,15 +121,13 @@ static bool batch_line_cfg(int es, int n, int nthreads, int mmax, int variant, S
     // each (32 lanes of 9-16 cells, two lines per wave); shorter lines do
     // better on the one-line tiles of capacity 4 or 8
     if (variant == SWEEP_FACE_SLOTS && mmax == 16 && n > 256 && (n + 31) / 32 <= 16 && nthreads >= 64) {
-        const int lpw = nthreads / 32;
-        if (sweep_lds(es, 2, n, lpw, 1, nthreads, 16, variant, 1) <= kLdsLimit) {
-            out->wpl = 1;
-            out->lpw = lpw;
-            out->P = 32;
-            out->mmax = 16;
-            out->io = 1;
-            out->variant = variant;
-            out->half = 1;
+        SweepCfg c;
+        c.lpl = 32;
+        c.lpw = nthreads / 32;
+        c.P = 32;
+        c.mmax = 16;
+        if (sweep_lds(es, 2, n, c) <= kLdsLimit) {
+            *out = c;
             return true;
         }
     }
@@ -141,13 +139,14 @@ static bool batch_line_cfg(int es, int n, int nthreads, int mmax, int variant, S
         // the tile's own capacity: mmax, mmax / 2, or (capacity 16) 4
         int own = mmax >= 4 && 2 * m <= mmax ? mmax / 2 : mmax;
         if (mmax == 16 && m <= 4) own = 4;
-        if (sweep_lds(es, 2, n, lpw, wpl, nthreads, own, variant) > kLdsLimit) continue;
-        out->wpl = wpl;
-        out->lpw = lpw;
-        out->P = P;
-        out->mmax = own;
-        out->variant = variant;
-        out->half = 0;
+        SweepCfg c;
+        c.wpl = wpl;
+        c.lpw = lpw;
+        c.P = P;
+        c.mmax = own;
+        c.variant = variant;
+        if (sweep_lds(es, 2, n, c) > kLdsLimit) continue;
+        *out = c;
         return true;
     }
     return false;
@@ -169,8 +168,7 @@ static int batch_shape(asd_batch b, int nthreads, int variant, int mmax_from = 4
                 const int n = (int)b->sub[p]->d.n[d];
                 ok = batch_line_cfg(es, n, nthreads, mmax, variant, &cfg[2 * p + d]);
                 if (ok)
-                    lds = std::max(lds, sweep_lds(es, 2, n, cfg[2 * p + d].lpw, cfg[2 * p + d].wpl, nthreads,
-                                                  cfg[2 * p + d].mmax, variant, cfg[2 * p + d].half));
+                    lds = std::max(lds, sweep_lds(es, 2, n, cfg[2 * p + d]));
             }
         }
         if (!ok) continue;
@@ -320,7 +318,7 @@ static int batch_tables(asd_batch b) {
             const int nt1 = probs[p].sweep[d].nt1, lpw = b->cfg[2 * p + d].lpw;
             probs[p].ngroups[d] = (nt1 + lpw - 1) / lpw;
             probs[p].mmax[d] = b->cfg[2 * p + d].mmax;
-            probs[p].half[d] = b->cfg[2 * p + d].half;
+            probs[p].half[d] = b->cfg[2 * p + d].lpl == 32;
         }
         probs[p].dirichlet = g->d.bc == ASD_BC_DIRICHLET;
         probs[p].dV = g->d.h[0] * g->d.h[1];

@@ -154,12 +154,13 @@ static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, floa
     }
     const void* in = g->T;
     int cur = 0;  // scratch buffer written next
+    const int mode = four_step_twice(g, cfg) ? SWEEP_TWICE : 0;
     auto chain = [&](int steps) {
         int rc = ASD_OK;
         for (int s = 0; s < steps && !rc; ++s)
             for (int d = 0; d < g->d.ndim && !rc; ++d) {
                 void* out = g->tmp[cur];
-                rc = enqueue_sweep(g, d, dt, in, out, 0, no_reduce(), &cfg[d], nullptr);
+                rc = enqueue_sweep(g, d, dt, in, out, mode, no_reduce(), &cfg[d], nullptr);
                 in = out;
                 cur ^= 1;
             }

@@ -408,11 +408,11 @@ int fill_sweep_params(asd_grid g, int d, const void* in, void* out, int rhs_mode
     P.lpw = c.lpw;
     P.P = c.P;
     P.nseg_log2 = ilog2(c.P);
-    P.spl_log2 = c.half ? 5 : ilog2(64 * c.wpl);
+    P.spl_log2 = ilog2(c.lpl * c.wpl);
     P.io_log2 = ilog2(c.io);
     P.lpw_log2 = ilog2(c.lpw);
     P.rhs_mode = rhs_mode & SWEEP_SOLVE_ONLY;
-    P.lds = sweep_layout((int)sizeof(T), g->d.ndim, P.n, c.lpw, c.wpl, c.nthreads(), c.mmax, c.variant, c.half);
+    P.lds = sweep_layout((int)sizeof(T), g->d.ndim, P.n, c, (rhs_mode & SWEEP_TWICE) != 0);
     if (P.si_n != 1) return asd_fail(ASD_EUNSUPPORTED, "sweep input must be contiguous along the line");
     *Pout = P;
     return ASD_OK;
@@ -424,7 +424,10 @@ template <typename T>
 static int enqueue_sweep_t(asd_grid g, int d, double dt, const void* in, void* out, int rhs_mode,
                            const ReduceParams& red, const SweepCfg* override_cfg, int* nblocks_out, void* out2) {
     // the coefficients were computed for dt by prepare() (or enqueue_coef)
-    const SweepCfg& c = override_cfg ? *override_cfg : g->cfg[d];
+    SweepCfg c = override_cfg ? *override_cfg : g->cfg[d];
+    const bool twice = (rhs_mode & SWEEP_TWICE) != 0;
+    if (twice && !twice_cfg((int)sizeof(T), g->d.ndim, (int)g->d.n[d], c, &c))
+        return asd_fail(ASD_EUNSUPPORTED, "the two-solve tile does not fit");
     SweepParams<T> P;
     int rc = fill_sweep_params<T>(g, d, in, out, rhs_mode, c, &P);
     if (rc) return rc;
@@ -445,9 +448,9 @@ static int enqueue_sweep_t(asd_grid g, int d, double dt, const void* in, void* o
     if (nblocks_out) *nblocks_out = (int)nblocks;
     if (red.partials && nblocks > g->max_blocks)
         return asd_fail(ASD_EUNSUPPORTED, "too many blocks for the reduction scratch");
-    const size_t lds = sweep_lds((int)sizeof(T), g->d.ndim, P.n, c.lpw, c.wpl, c.nthreads(), c.mmax, c.variant, c.half);
+    const size_t lds = (size_t)P.lds.total;
     return hip_check(launch_sweep<T>(P, g->d.ndim, c.mmax, dim3((unsigned)nblocks), dim3(c.nthreads()), lds, g->st,
-                                     c.variant),
+                                     c.variant, twice),
                      "sweep launch");
 }
 
@@ -514,27 +517,41 @@ int check_dt(asd_grid g, double dt, bool explicit_scheme) {
 // slot, and one fold launch turns a full ring (or the last steps) into the
 // outputs of each of those steps, off the sweeps' critical path.
 // Workgroups of one launch of sweep d in the grid's current launch shape.
-static int64_t sweep_num_blocks(asd_grid g, int d) {
+static int64_t sweep_num_blocks(asd_grid g, int d, bool twice) {
     const SweepGeom G = sweep_geom(g->d.ndim, d);
     const int64_t nz = g->d.ndim == 3 ? g->d.n[2] : 1;
     const int64_t nax[3] = {g->d.n[0], g->d.n[1], nz};
-    const int lpw = g->cfg[d].lpw;
+    SweepCfg c = g->cfg[d];
+    if (twice) (void)twice_cfg((int)g->es, g->d.ndim, (int)g->d.n[d], c, &c);
+    const int lpw = c.lpw;
     return (nax[G.t1] + lpw - 1) / lpw * nax[G.t2];
+}
+
+bool four_step_twice(asd_grid g, const SweepCfg* cfg) {
+    if (!(g->d.flags & ASD_FLAG_FOUR_STEP) || g->d.chi_exp != 0.0) return false;
+    SweepCfg c;
+    for (int d = 0; d < g->d.ndim; ++d)
+        if (!twice_cfg((int)g->es, g->d.ndim, (int)g->d.n[d], cfg[d], &c)) return false;
+    return true;
 }
 
 int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     const int nd = g->d.ndim;
-    const bool four = (g->d.flags & ASD_FLAG_FOUR_STEP) != 0;
+    // 4-step: each direction's two solves in one launch where the tile fits
+    // (256^3 FP32: one pass over memory instead of two), else in two
+    const bool twice = four_step_twice(g, g->cfg);
+    const bool four = (g->d.flags & ASD_FLAG_FOUR_STEP) != 0 && !twice;
+    const int tw = twice ? SWEEP_TWICE : 0;
     const bool reverse = (g->d.flags & ASD_FLAG_REVERSE_ORDER) != 0;  // 2-D only
     int rc = ASD_OK;
     // The initial state's energy: reduced by the first sweep, which reads
-    // every cell of it once (2-step scheme in the order x, y, no source), and
+    // every cell of it once (one launch per direction in the order x, y, no source), and
     // folded before the first steps' fold; else by a standalone reduction.
     const bool fuse_e0 = outs.any() && nsteps > 0 && !four && !reverse && !g->src;
     // when the first sweep and the step's last sweep launch as many blocks,
     // the initial state's partials take ring slot 0 and are folded with the
     // first steps' (one fold launch fewer per call)
-    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0) == sweep_num_blocks(g, g->d.ndim - 1);
+    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0, twice) == sweep_num_blocks(g, g->d.ndim - 1, twice);
     FoldParams f0{};
     bool f0_pending = false;
     if (outs.any() && !fuse_e0) {
@@ -569,14 +586,14 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
                 // intermediate (input layout) goes to T, free meanwhile.
                 out = d == 1 ? g->tmp[0] : g->tmp[1];
                 if (!four) {
-                    rc = sweep(d, in, out, src, red, &nb);
+                    rc = sweep(d, in, out, src | tw, red, &nb);
                 } else {
                     rc = sweep(d, in, g->T, SWEEP_KEEP_LAYOUT | src, no_reduce(), nullptr);
                     if (rc == ASD_OK) rc = sweep(d, g->T, out, SWEEP_SOLVE_ONLY, red, &nb);
                 }
             } else if (!four) {
                 out = (d == nd - 1) ? g->T : g->tmp[d];
-                rc = sweep(d, in, out, src | (red_in ? SWEEP_REDUCE_INPUT : 0), red, &nb);
+                rc = sweep(d, in, out, src | tw | (red_in ? SWEEP_REDUCE_INPUT : 0), red, &nb);
                 if (red_in && !e0_in_ring) {
                     f0 = make_fold(g, red.partials, nb, 1, outs, 0);
                     f0_pending = true;

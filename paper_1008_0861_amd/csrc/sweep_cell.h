@@ -55,6 +55,7 @@
 
 #include "asd_device.h"
 #include "asd_launch.h"
+#include "wave_pcr.h"
 
 namespace asd {
 namespace cell {
@@ -244,11 +245,17 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
     const int ok1 = ctx.ok1, ostep1 = ctx.ostep1;
 
     // ---------------- phase 2: per-lane segment elimination
-    // Segments are interleaved over the line's waves: lane l of wave w owns
-    // segment kseg = l * wpl + w.
+    // Segments are interleaved over the line's waves: row j of wave w owns
+    // segment kseg = j * wpl + w.  On aligned tiles (64 wpl segments) a wave's
+    // rows sit on its lanes in the order of wave_pcr.h, else row j in lane j.
     const int wpl_log2 = spl_log2 - 6;
     const int nseg = 1 << P.nseg_log2;
-    const int kseg = ((k & 63) << wpl_log2) | (k >> 6);
+    const int wrow = FULL ? row_of_lane(k & 63) : k & 63;
+    const int kseg = (wrow << wpl_log2) | (k >> 6);
+    auto row_lane = [&](int j) {  // the lane of row j (mod the wave's rows)
+        if constexpr (FULL) return lane_of_row(j);
+        else return j & ((nseg >> wpl_log2) - 1);
+    };
     const bool active = line_ok && kseg < nseg;
     const int s0 = active ? (kseg * n) >> P.nseg_log2 : 0;
     const int m = FULL ? MMAX : (active ? (((kseg + 1) * n) >> P.nseg_log2) - s0 : 1);
@@ -366,8 +373,8 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
     // right neighbour's first-cell expression (Y, Uc, V).
     T Ra, Rc, Rd, XR, XL;
     if (P.wpl == 1) {
-        // one wave per line: lane == segment; shuffles only, no barrier
-        const int kr = (k + 1) & (nseg - 1);
+        // one wave per line: no exchange between waves
+        const int kr = row_lane(wrow + 1);
         const T Yp = __shfl(Y, kr, 64), Up = __shfl(Uc, kr, 64), Vp = __shfl(V, kr, 64);
         if (active) {
             const T ib = fast_rcp<T>(be - ae * hp + ce * Up);
@@ -377,31 +384,21 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
         } else {
             Ra = T(0); Rc = T(0); Rd = T(0);
         }
-        for (int s = 1; s < nseg; s <<= 1) {
-            const int km = (k - s) & (nseg - 1), kp = (k + s) & (nseg - 1);
-            const T am = __shfl(Ra, km, 64), cm = __shfl(Rc, km, 64), dm = __shfl(Rd, km, 64);
-            const T ap = __shfl(Ra, kp, 64), cp = __shfl(Rc, kp, 64), dp = __shfl(Rd, kp, 64);
-            if (k < nseg) {
-                const T ib = fast_rcp<T>(T(1) - Ra * cm - Rc * ap);
-                const T na = -Ra * am, nc = -Rc * cp, nd = Rd - Ra * dm - Rc * dp;
-                Ra = na * ib;
-                Rc = nc * ib;
-                Rd = nd * ib;
-            }
-        }
+        if constexpr (FULL) pcr_wave64<T>(wrow, Ra, Rc, Rd);
+        else pcr_lanes<T>(k & 63, nseg, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
-        XL = __shfl(XR, (k - 1) & (nseg - 1), 64);
+        XL = __shfl(XR, row_lane(wrow - 1), 64);
     } else {
         // several waves per line.  Exchanges between waves go through two
         // LDS buffers used alternately: a buffer is rewritten only after the
         // barrier that follows the last reads of it, so each exchange costs
         // one barrier.  Segment j's entry sits at the index of the thread
-        // that owns it, (j mod wpl)*64 + j/wpl: a wave's stores are
-        // contiguous.
+        // that owns it: a wave's stores are contiguous.
         const int lb = q * spl;
         const int wmask = P.wpl - 1;
         auto slot = [&](int b, int j) -> unsigned char* {
-            const int t = ((j & wmask) << 6) + (j >> wpl_log2);
+            const int jr = j >> wpl_log2;
+            const int t = ((j & wmask) << 6) + (FULL ? lane_of_row(jr) : jr);
             if (b == 0) return smem + Lo.pcr0_at + (lb + t) * SLOT;
             return Lo.pcr1_at < 0 ? row1 + cell_off1(t, ES, pad) : smem + Lo.pcr1_at + (lb + t) * SLOT;
         };
@@ -491,22 +488,9 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
                 Rd = nd * ib;
             }
         }
-        // strides wpl and up: partners are lanes of this wave, s / wpl apart
-        // (the line's nseg / wpl segments of this wave sit in its first lanes)
-        const int lane = k & 63;
-        for (int s = P.wpl; s < nseg; s <<= 1) {
-            const int nl = nseg >> wpl_log2, sl = s >> wpl_log2;
-            const int lm = (lane - sl) & (nl - 1), lp = (lane + sl) & (nl - 1);
-            const T am = __shfl(Ra, lm, 64), cm = __shfl(Rc, lm, 64), dm = __shfl(Rd, lm, 64);
-            const T ap = __shfl(Ra, lp, 64), cp = __shfl(Rc, lp, 64), dp = __shfl(Rd, lp, 64);
-            if (active) {
-                const T ib = fast_rcp<T>(T(1) - Ra * cm - Rc * ap);
-                const T na = -Ra * am, nc = -Rc * cp, nd = Rd - Ra * dm - Rc * dp;
-                Ra = na * ib;
-                Rc = nc * ib;
-                Rd = nd * ib;
-            }
-        }
+        // strides wpl and up: partners are rows of this wave, s / wpl apart
+        if constexpr (FULL) pcr_wave64<T>(wrow, Ra, Rc, Rd);
+        else pcr_lanes<T>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         cur ^= 1;
         *reinterpret_cast<T*>(slot(cur, kseg)) = XR;

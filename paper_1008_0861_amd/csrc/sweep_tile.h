@@ -56,6 +56,7 @@
 
 #include "asd_device.h"
 #include "asd_launch.h"
+#include "wave_pcr.h"
 
 namespace asd {
 
@@ -102,9 +103,10 @@ struct TileCtx {
     int neg1m, neg1p, neg2m, neg2p;  // T = 0 walls: that transverse neighbour is the odd ghost
 };
 
-// HALF: two lines per wave (lanes 0-31 and 32-63), a line's solve spread
-// over 32 lanes (short lines in batches); the line index is then per lane.
-template <typename T, int NDIM, bool EXT, bool HALF = false>
+// LPL: lanes of a wave per line.  64: a line is owned by whole waves.  32:
+// two lines per wave (lanes 0-31 and 32-63), a line's solve spread over 32
+// lanes (short lines in batches); the line index is then per lane.
+template <typename T, int NDIM, bool EXT, int LPL = 64>
 __device__ __forceinline__ TileCtx<T> tile_ctx(const SweepParams<T>& P, int l1_0, int l2, unsigned char* buf) {
     const int sio_log2 = P.spl_log2 + P.io_log2;
     const bool periodic = P.periodic != 0;
@@ -112,9 +114,9 @@ __device__ __forceinline__ TileCtx<T> tile_ctx(const SweepParams<T>& P, int l1_0
     TileCtx<T> c;
     c.l1_0 = l1_0;
     c.l2 = l2;
-    if constexpr (HALF) {
+    if constexpr (LPL < 64) {
         c.q = (int)threadIdx.x >> 5;
-        c.k = threadIdx.x & 31;
+        c.k = threadIdx.x & (LPL - 1);
         c.w = 0;
         c.lane = c.k;
     } else {
@@ -174,11 +176,11 @@ struct ChunkData {
 // Cell n is cell 0 on a periodic line (the wrap neighbour); cells past the
 // line's end are otherwise clamped to its last cell (their values are not
 // used).
-template <typename T, int NDIM, bool HALF = false>
+template <typename T, int NDIM, int LPL = 64>
 __device__ __forceinline__ void load_chunk(const SweepParams<T>& P, const TileCtx<T>& c, int chunk, bool face,
                                            ChunkData<T>& r) {
     constexpr int ES = (int)sizeof(T);
-    constexpr int CL = HALF ? 5 : 6;  // log2 of the cells per chunk (lanes per line)
+    constexpr int CL = LPL == 64 ? 6 : 5;  // log2 of the cells per chunk (lanes per line)
     const bool solve_only = P.rhs_mode != 0;
     const int n = P.n;
     int p = (chunk << CL) + c.lane;
@@ -207,11 +209,11 @@ template <typename T>
 __device__ __forceinline__ T rotate_down(T v) {
     return dpp_mov<0x134, 0xf>(v, v);
 }
-// The same within each half of the wave (lane i takes lane i+1 mod 32 of
-// its half): two lines per wave.
-template <typename T>
-__device__ __forceinline__ T rotate_down_half(T v, int lane32) {
-    return __shfl(v, (lane32 + 1) & 31, 32);
+// The same within each group of LPL lanes.
+template <typename T, int LPL>
+__device__ __forceinline__ T rotate_down_line(T v, int lane) {
+    if constexpr (LPL == 64) return rotate_down<T>(v);
+    else return __shfl(v, (lane + 1) & (LPL - 1), LPL);
 }
 
 // Stages the tile's faces: for every cell p of the line,
@@ -219,16 +221,16 @@ __device__ __forceinline__ T rotate_down_half(T v, int lane32) {
 // and (alpha_f, Phi_f) into the face's slot.  Loads go in batches of up to
 // nine chunks; the last chunk of a batch waits for the next batch's first
 // (its lane 63 needs it).
-template <typename T, int NDIM, int MMAX, int LIMC, bool EXT, bool HALF = false>
+template <typename T, int NDIM, int MMAX, int LIMC, bool EXT, int LPL = 64, bool TW = false>
 __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCtx<T>& c) {
     constexpr int ES = (int)sizeof(T);
-    constexpr int CL = HALF ? 5 : 6;  // log2 of the cells per chunk
-    auto rot = [&](T v) { return HALF ? rotate_down_half<T>(v, c.lane) : rotate_down<T>(v); };
+    constexpr int CL = LPL == 64 ? 6 : 5;  // log2 of the cells per chunk
+    auto rot = [&](T v) { return rotate_down_line<T, LPL>(v, c.lane); };
     constexpr int CH = MMAX < 8 ? MMAX + 1 : 9;
     const bool solve_only = P.rhs_mode != 0;
     const int lim = LIMC >= 0 ? LIMC : P.limiter;
     const int n = P.n;
-    const int wio_log2 = HALF ? 0 : P.spl_log2 + P.io_log2 - 6;  // staging waves per line: wpl * io
+    const int wio_log2 = LPL < 64 ? 0 : P.spl_log2 + P.io_log2 - 6;  // staging waves per line: wpl * io
     const int nch = (n + (1 << CL) - 1) >> CL;
     const int cpw = (nch + (1 << wio_log2) - 1) >> wio_log2;
     const int c0 = c.w * cpw;
@@ -246,7 +248,7 @@ __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCt
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
             const int jj = j0 + j;  // chunk jj of the wave; jj == jn: the extra chunk
-            if (jj <= jn) load_chunk<T, NDIM, HALF>(P, c, jj < jn ? c0 + jj : cnext, jj < jn, r[j]);
+            if (jj <= jn) load_chunk<T, NDIM, LPL>(P, c, jj < jn ? c0 + jj : cnext, jj < jn, r[j]);
         }
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
@@ -276,7 +278,12 @@ __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCt
                 if (p < n) {
                     T a = pa;
                     T phi = a * (un - pu);
-                    if (!solve_only) {
+                    T F = T(0);
+                    if (TW) {  // the transverse part alone (never a solve-only sweep)
+                        F = pb1 * limit2<T>(lim, last_lane ? nrs1 : rs1, ps1);
+                        if (NDIM == 3) F += pb2 * limit2<T>(lim, last_lane ? nrs2 : rs2, ps2);
+                        phi += F;
+                    } else if (!solve_only) {
                         phi += pb1 * limit2<T>(lim, last_lane ? nrs1 : rs1, ps1);
                         if (NDIM == 3) phi += pb2 * limit2<T>(lim, last_lane ? nrs2 : rs2, ps2);
                     }
@@ -285,8 +292,10 @@ __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCt
                         // line's two wall coefficients, read by the solve
                         a = T(0);
                         phi = T(0);
+                        F = T(0);
                     }
-                    lds_put_pair<T>(c.row1 + slot_off(p, ES, P.lds.pad), a, phi);
+                    if (TW) lds_put4<T>(c.row1 + cell_off1(p, ES, P.lds.pad), a, phi, F, T(0));
+                    else lds_put_pair<T>(c.row1 + slot_off(p, ES, P.lds.pad), a, phi);
                 }
             }
             pu = u;
@@ -309,11 +318,17 @@ __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCt
 // tile layout), so the segment length is a compile-time constant and the
 // per-cell bounds tests vanish.  REUSE: the block stages another tile in
 // the same LDS afterwards (a closing barrier).
-template <typename T, int NDIM, int MMAX, int LIMC, bool EXT, bool FULL, bool REUSE, bool HALF = false>
+//
+// TW (the 4-step scheme, Eq. 4step): two solves with the same matrix, at
+// half the time step each.  With A d1 = L U + S (L the normal operator,
+// S = F_{+} - F_{-} + dt Q, A = 1 - L), the second solve's right-hand side
+// L (U + d1) equals d1 - S, so the tile holds all it needs: A d2 = d1 - S,
+// out = U + d1 + d2.
+template <typename T, int NDIM, int MMAX, int LIMC, bool EXT, bool FULL, bool REUSE, int LPL = 64, bool TW = false>
 __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileCtx<T>& ctx, unsigned char* smem,
                                             const T (&uu)[MMAX], double& lsum, T& lmin, T& lmax) {
     constexpr int ES = (int)sizeof(T);
-    constexpr int SLOT = 2 * ES;   // bytes of a face slot
+    constexpr int SLOT = TW ? 4 * ES : 2 * ES;  // bytes of a face slot
     constexpr int XSLOT = 4 * ES;  // bytes of an exchange entry
     const int n = P.n;
     const int lpw = P.lpw;
@@ -322,24 +337,33 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
     const int nthreads = blockDim.x;
     const TileLayout& Lo = P.lds;
     const int pad = Lo.pad;
+    auto soff = [&](int p) { return TW ? cell_off1(p, ES, pad) : slot_off(p, ES, pad); };
     const int spl_log2 = P.spl_log2;
     const int q = ctx.q, k = ctx.k, l1 = ctx.l1, l1_0 = ctx.l1_0, l2 = ctx.l2;
     const bool line_ok = ctx.line_ok;
     unsigned char* row1 = ctx.row1;
 
     // ---------------- phase 2: per-lane segment elimination
-    // Segments are interleaved over the line's waves: lane l of wave w owns
-    // segment kseg = l * wpl + w.
-    const int wpl_log2 = HALF ? 0 : spl_log2 - 6;
-    constexpr int SW = HALF ? 32 : 64;  // lanes that exchange by shuffles: one line's
+    // Segments are interleaved over the line's waves: row j of wave w owns
+    // segment kseg = j * wpl + w.  On aligned tiles (64 wpl segments) a wave's
+    // rows sit on its lanes in the order of wave_pcr.h, else row j in lane j.
+    const int wpl_log2 = LPL < 64 ? 0 : spl_log2 - 6;
+    constexpr bool ROWS = FULL && LPL == 64;
     const int sio_log2 = spl_log2 + P.io_log2;
     const int nseg = 1 << P.nseg_log2;
     const bool part = k < spl;  // this thread takes part in the solve
-    const int kseg = HALF ? k : ((k & 63) << wpl_log2) | (k >> 6);
+    const int wrow = ROWS ? row_of_lane(k & 63) : k & 63;
+    const int kseg = LPL < 64 ? k : (wrow << wpl_log2) | (k >> 6);
+    // the lane of row j (mod the wave's rows of this line)
+    auto row_lane = [&](int j) {
+        if constexpr (ROWS) return lane_of_row(j);
+        else if constexpr (LPL < 64) return ((int)threadIdx.x & 63 & ~(LPL - 1)) | (j & (LPL - 1));
+        else return j & ((nseg >> wpl_log2) - 1);
+    };
     const bool active = part && line_ok && kseg < nseg;
     const int s0 = active ? (FULL ? kseg * MMAX : (kseg * n) >> P.nseg_log2) : 0;
     const int m = FULL ? MMAX : (active ? (((kseg + 1) * n) >> P.nseg_log2) - s0 : 1);
-    const int os0 = slot_off(s0, ES, pad);  // the segment's first slot
+    const int os0 = soff(s0);  // the segment's first slot
 
     // The faces of the segment: index 0 is the face before cell s0 (the last
     // face of the previous segment, or the wrap face), index i+1 the face
@@ -347,10 +371,19 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
     // from the row's spare slots and ignored).  The segment's own slots are
     // consecutive.  All reads are issued before any arithmetic.
     T fa[MMAX + 1], fp[MMAX + 1];
+    T S[TW ? MMAX : 1];  // F_{+} - F_{-} + dt Q of the segment's cells
     {
         int jl = s0 - 1;
         if (jl < 0) jl += n;
-        lds_get_pair<T>(row1 + slot_off(jl, ES, pad), fa[0], fp[0]);
+        if constexpr (TW) {
+            T fF[MMAX + 1], unused;
+            lds_get4<T>(row1 + soff(jl), fa[0], fp[0], fF[0], unused);
+#pragma unroll
+            for (int c = 0; c < MMAX; ++c) lds_get4<T>(row1 + os0 + c * SLOT, fa[c + 1], fp[c + 1], fF[c + 1], unused);
+#pragma unroll
+            for (int c = 0; c < MMAX; ++c) S[c] = fF[c + 1] - fF[c];
+        } else {
+        lds_get_pair<T>(row1 + soff(jl), fa[0], fp[0]);
         if constexpr (FULL && (MMAX % 2) == 0) {
 #pragma unroll
             for (int c = 0; c < MMAX; c += 2)
@@ -358,6 +391,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
         } else {
 #pragma unroll
             for (int c = 0; c < MMAX; ++c) lds_get_pair<T>(row1 + os0 + c * SLOT, fa[c + 1], fp[c + 1]);
+        }
         }
     }
 
@@ -376,7 +410,11 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
             const T* lineQ = P.Q + ctx.base;
 #pragma unroll
             for (int i = 0; i < MMAX; ++i)
-                if (i < m) rv[i] += P.dtq * lineQ[s0 + i];
+                if (i < m) {
+                    const T dq = P.dtq * lineQ[s0 + i];
+                    rv[i] += dq;
+                    if (TW) S[i] += dq;
+                }
         }
         if (P.dirichlet) {
             // T = 0 walls: the wall faces of the line's first and last cells
@@ -400,6 +438,9 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
             }
         }
     }
+    T d1[TW ? MMAX : 1];  // the first solve's increments
+#pragma unroll 1
+    for (int pass = 0; pass < (TW ? 2 : 1); ++pass) {
     T ae = av[MMAX - 1], be = bv[MMAX - 1], ce = cv[MMAX - 1], re = rv[MMAX - 1];  // row of the last cell
     if (!FULL) {
 #pragma unroll
@@ -447,9 +488,9 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
     // right neighbour's first-cell expression (Y, Uc, V).
     T Ra, Rc, Rd, XR, XL;
     if (P.wpl == 1) {
-        // one wave per line: lane == segment; shuffles only, no barrier
-        const int kr = (k + 1) & (nseg - 1);
-        const T Yp = __shfl(Y, kr, SW), Up = __shfl(Uc, kr, SW), Vp = __shfl(V, kr, SW);
+        // one wave per line (or part of one): no exchange between waves
+        const int kr = row_lane(wrow + 1);
+        const T Yp = __shfl(Y, kr, 64), Up = __shfl(Uc, kr, 64), Vp = __shfl(V, kr, 64);
         if (active) {
             const T ib = fast_rcp<T>(be - ae * hp + ce * Up);
             Ra = ae * wp * ib;
@@ -458,27 +499,16 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
         } else {
             Ra = T(0); Rc = T(0); Rd = T(0);
         }
-        for (int s = 1; s < nseg; s <<= 1) {
-            const int km = (k - s) & (nseg - 1), kp = (k + s) & (nseg - 1);
-            const T am = __shfl(Ra, km, SW), cm = __shfl(Rc, km, SW), dm = __shfl(Rd, km, SW);
-            const T ap = __shfl(Ra, kp, SW), cp = __shfl(Rc, kp, SW), dp = __shfl(Rd, kp, SW);
-            if (k < nseg) {
-                const T ib = fast_rcp<T>(T(1) - Ra * cm - Rc * ap);
-                const T na = -Ra * am, nc = -Rc * cp, nd = Rd - Ra * dm - Rc * dp;
-                Ra = na * ib;
-                Rc = nc * ib;
-                Rd = nd * ib;
-            }
-        }
+        if constexpr (ROWS) pcr_wave64<T>(wrow, Ra, Rc, Rd);
+        else pcr_lanes<T>((int)threadIdx.x & 63, nseg, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
-        XL = __shfl(XR, (k - 1) & (nseg - 1), SW);
+        XL = __shfl(XR, row_lane(wrow - 1), 64);
     } else {
         // several waves per line.  Exchanges between waves go through two
         // LDS buffers used alternately: a buffer is rewritten only after the
         // barrier that follows the last reads of it, so each exchange costs
         // one barrier.  Segment j's entry sits at the index of the thread
-        // that owns it, (j mod wpl)*64 + j/wpl: a wave's stores are
-        // contiguous.
+        // that owns it: a wave's stores are contiguous.
         // Segments of MMAX >= 8 cells on an aligned tile keep both buffers
         // in their own face slots 4..7, which only the owner reads before
         // the first exchange (the last face slot, which the next segment
@@ -489,8 +519,9 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
         unsigned char* const xbuf0 = smem + Lo.pcr0_at + lb * XSLOT;
         unsigned char* const xbuf1 = smem + Lo.pcr1_at + lb * XSLOT;
         auto xslot = [&](int b, int j) -> unsigned char* {
-            if constexpr (INSLOT) return row1 + slot_off(j * MMAX, ES, pad) + (4 + 2 * b) * SLOT;
-            const int t = ((j & wmask) << 6) + (j >> wpl_log2);
+            if constexpr (INSLOT) return row1 + soff(j * MMAX) + (4 + 2 * b) * SLOT;
+            const int jr = j >> wpl_log2;
+            const int t = ((j & wmask) << 6) + (ROWS ? lane_of_row(jr) : jr);
             return (b == 0 ? xbuf0 : xbuf1) + t * XSLOT;
         };
         int cur = 0;
@@ -521,9 +552,9 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
                     rc = a2 * vp * ib;
                     rd = (a4 - a2 * yp) * ib;
                 };
-                const int om = slot_off(((kseg - 1) & (nseg - 1)) * MMAX, ES, pad);
-                const int op1 = slot_off(((kseg + 1) & (nseg - 1)) * MMAX, ES, pad);
-                const int op2 = slot_off(((kseg + 2) & (nseg - 1)) * MMAX, ES, pad);
+                const int om = soff(((kseg - 1) & (nseg - 1)) * MMAX);
+                const int op1 = soff(((kseg + 1) & (nseg - 1)) * MMAX);
+                const int op2 = soff(((kseg + 2) & (nseg - 1)) * MMAX);
                 T m1, m2, m3, m4, q1, q2, q3, q4, y1, u1, v1, y2, u2, v2, unused;
                 lds_get4<T>(row1 + om, m1, m2, m3, m4);
                 lds_get4<T>(row1 + op1, q1, q2, q3, q4);
@@ -572,22 +603,9 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
                 Rd = nd * ib;
             }
         }
-        // strides wpl and up: partners are lanes of this wave, s / wpl apart
-        // (the line's nseg / wpl segments of this wave sit in its first lanes)
-        const int lane = k & 63;
-        for (int s = P.wpl; s < nseg; s <<= 1) {
-            const int nl = nseg >> wpl_log2, sl = s >> wpl_log2;
-            const int lm = (lane - sl) & (nl - 1), lp = (lane + sl) & (nl - 1);
-            const T am = __shfl(Ra, lm, 64), cm = __shfl(Rc, lm, 64), dm = __shfl(Rd, lm, 64);
-            const T ap = __shfl(Ra, lp, 64), cp = __shfl(Rc, lp, 64), dp = __shfl(Rd, lp, 64);
-            if (active) {
-                const T ib = fast_rcp<T>(T(1) - Ra * cm - Rc * ap);
-                const T na = -Ra * am, nc = -Rc * cp, nd = Rd - Ra * dm - Rc * dp;
-                Ra = na * ib;
-                Rc = nc * ib;
-                Rd = nd * ib;
-            }
-        }
+        // strides wpl and up: partners are rows of this wave, s / wpl apart
+        if constexpr (ROWS) pcr_wave64<T>(wrow, Ra, Rc, Rd);
+        else pcr_lanes<T>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         cur ^= 1;
         if (part) *reinterpret_cast<T*>(xslot(cur, kseg)) = XR;
@@ -597,7 +615,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
 
     // ---------------- back substitution: each cell's increment goes into the
     // second element of its face slot (no exchange reads those after this)
-    if (active) {
+    if (TW && pass == 0) {
         T dn = XR;
 #pragma unroll
         for (int i = MMAX - 1; i >= 0; --i) {
@@ -605,9 +623,23 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
                 T d = XR;
                 if (i < MMAX - 1 && (FULL || i != m - 1)) d = gv[i] - hv[i] * dn + wv[i] * XL;
                 dn = d;
-                *reinterpret_cast<T*>(row1 + os0 + i * SLOT + ES) = d;
+                d1[i] = d;
+                rv[i] = d - S[i];
             }
         }
+        if (P.wpl > 1) __syncthreads();  // the exchange buffers are used again
+    } else if (active) {
+        T dn = XR;
+#pragma unroll
+        for (int i = MMAX - 1; i >= 0; --i) {
+            if (FULL || i < m) {
+                T d = XR;
+                if (i < MMAX - 1 && (FULL || i != m - 1)) d = gv[i] - hv[i] * dn + wv[i] * XL;
+                dn = d;
+                *reinterpret_cast<T*>(row1 + os0 + i * SLOT + ES) = TW ? d1[i] + d : d;
+            }
+        }
+    }
     }
     __syncthreads();
 
@@ -637,7 +669,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
             if (p >= n) break;
             if (qq_ok) {
                 T unused, d;
-                lds_get_pair<T>(rq + slot_off(p, ES, pad), unused, d);
+                lds_get_pair<T>(rq + soff(p), unused, d);
                 const T x = uu[it] + d;
                 // 2-D: a 32-bit byte offset from the uniform base (a 2-D field
                 // stays below 4 GiB); 3-D: a 32-bit element index
@@ -662,7 +694,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
             const int p = k + (it << sio_log2);
             if (p >= n) break;
             T unused, d;
-            lds_get_pair<T>(row1 + slot_off(p, ES, pad), unused, d);
+            lds_get_pair<T>(row1 + soff(p), unused, d);
             const T x = uu[it] + d;
             ob[(unsigned)(p * P.so_n)] = x;
             if (reduce) {
@@ -711,20 +743,20 @@ __device__ __forceinline__ void load_store_u(const SweepParams<T>& P, const Tile
 
 // One whole tile (phases 1-3) in the LDS buffer at smem.  REUSE: the caller
 // stages further tiles in the same LDS afterwards.
-template <typename T, int NDIM, int MMAX, int LIMC, bool EXT = false, bool REUSE = false, bool HALF = false>
+template <typename T, int NDIM, int MMAX, int LIMC, bool EXT = false, bool REUSE = false, int LPL = 64, bool TW = false>
 __device__ __forceinline__ void sweep_tile(const SweepParams<T>& P, int l1_0, int l2, unsigned char* smem,
                                            double& lsum, T& lmin, T& lmax) {
-    const TileCtx<T> c = tile_ctx<T, NDIM, EXT, HALF>(P, l1_0, l2, smem);
-    stage_tile<T, NDIM, MMAX, LIMC, EXT, HALF>(P, c);
+    const TileCtx<T> c = tile_ctx<T, NDIM, EXT, LPL>(P, l1_0, l2, smem);
+    stage_tile<T, NDIM, MMAX, LIMC, EXT, LPL, TW>(P, c);
     // U of the cells this thread stores in phase 3 (same lines, still in
     // cache): loaded now, so that the solve hides their latency
     T uu[MMAX];
     load_store_u<T, MMAX>(P, c, uu);
     __syncthreads();
     if (P.lds.aligned)
-        solve_store<T, NDIM, MMAX, LIMC, EXT, true, REUSE, HALF>(P, c, smem, uu, lsum, lmin, lmax);
+        solve_store<T, NDIM, MMAX, LIMC, EXT, true, REUSE, LPL, TW>(P, c, smem, uu, lsum, lmin, lmax);
     else
-        solve_store<T, NDIM, MMAX, LIMC, EXT, false, REUSE, HALF>(P, c, smem, uu, lsum, lmin, lmax);
+        solve_store<T, NDIM, MMAX, LIMC, EXT, false, REUSE, LPL, TW>(P, c, smem, uu, lsum, lmin, lmax);
 }
 
 }  // namespace asd
