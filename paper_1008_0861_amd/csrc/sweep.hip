@@ -104,9 +104,12 @@ __global__ void __launch_bounds__((SweepCellBounds<T, MMAX>::max_threads))
     if (P.red.partials) block_partials<T>(P.red.partials, lsum, lmin, lmax);
 }
 
-// Van Leer (the default limiter) gets its own straight-line instantiation;
-// the other limiters share one that reads the limiter at run time, and T = 0
-// walls or a source take a third that also reads those.
+// Van Leer, minmod and MC get straight-line instantiations of their own; the
+// linear mean reads the limiter at run time.  T = 0 walls, a source or a
+// second output take the EXT instantiations, van Leer's or the run-time one.
+// (A limiter read at run time costs several branches per face: 129^2 FP64
+// with walls and a source, van Leer, 7.1 us per sweep; see the launcher's
+// users for the straight-line times.)
 template <typename T, int NDIM>
 hipError_t launch_sweep_dim(const SweepParams<T>& P, int mmax, dim3 grid, dim3 block, size_t lds, hipStream_t st,
                             int variant) {
@@ -125,10 +128,16 @@ hipError_t launch_sweep_dim(const SweepParams<T>& P, int mmax, dim3 grid, dim3 b
 #define ASD_SWEEP_ARGS P.U, P.alpha, P.beta1, P.n, P.nt1, P.si_t1, P.si_t2, nb1, (int)grid.x, packed, P.lds.row1, P
 #define ASD_SWEEP_LAUNCH(KERNEL, MM)                                                                          \
     do {                                                                                                      \
-        if (ext)                                                                                              \
+        if (ext && P.limiter == LIM_VANLEER)                                                                  \
+            hipLaunchKernelGGL((KERNEL<T, NDIM, MM, LIM_VANLEER, true>), grid, block, lds, st, ASD_SWEEP_ARGS); \
+        else if (ext)                                                                                         \
             hipLaunchKernelGGL((KERNEL<T, NDIM, MM, -1, true>), grid, block, lds, st, ASD_SWEEP_ARGS);        \
         else if (P.limiter == LIM_VANLEER)                                                                    \
             hipLaunchKernelGGL((KERNEL<T, NDIM, MM, LIM_VANLEER, false>), grid, block, lds, st, ASD_SWEEP_ARGS); \
+        else if (P.limiter == LIM_MINMOD)                                                                     \
+            hipLaunchKernelGGL((KERNEL<T, NDIM, MM, LIM_MINMOD, false>), grid, block, lds, st, ASD_SWEEP_ARGS); \
+        else if (P.limiter == LIM_MC)                                                                         \
+            hipLaunchKernelGGL((KERNEL<T, NDIM, MM, LIM_MC, false>), grid, block, lds, st, ASD_SWEEP_ARGS);   \
         else                                                                                                  \
             hipLaunchKernelGGL((KERNEL<T, NDIM, MM, -1, false>), grid, block, lds, st, ASD_SWEEP_ARGS);       \
     } while (0)
@@ -200,7 +209,10 @@ static hipError_t set_attrs_lim(int bytes) {
 template <typename T, int NDIM>
 hipError_t set_attrs_dim(int bytes) {
     hipError_t e = set_attrs_lim<T, NDIM, LIM_VANLEER, false>(bytes);
+    if (e == hipSuccess) e = set_attrs_lim<T, NDIM, LIM_MINMOD, false>(bytes);
+    if (e == hipSuccess) e = set_attrs_lim<T, NDIM, LIM_MC, false>(bytes);
     if (e == hipSuccess) e = set_attrs_lim<T, NDIM, -1, false>(bytes);
+    if (e == hipSuccess) e = set_attrs_lim<T, NDIM, LIM_VANLEER, true>(bytes);
     if (e == hipSuccess) e = set_attrs_lim<T, NDIM, -1, true>(bytes);
     return e;
 }
