@@ -122,6 +122,83 @@ inline bool twice_cfg(int es, int ndim, int n, SweepCfg c, SweepCfg* out) {
     return true;
 }
 
+// Default launch shape of a sweep of `lines` lines of n cells.  Each choice
+// is the measured best over sizes (us per step, all sweeps alike):
+// - Lines per workgroup: pieces of at most 16 bytes in the transposed store
+//   (longer ones leave CUs idle or one workgroup per CU: FP32 1024^2 16.6 with
+//   4 lines, 18.9 with 8), fewer where that keeps more CUs busy.  units(l) is
+//   the number of lines of the busiest of the 256 CUs; l grows while it costs
+//   at most a third more: FP32 256^2 7.0 with 1 line, 7.4 with 4; 1200^2 26.6
+//   with 2, over 30 with 4; 4096^2 193 with 4, 436 with 1.
+// - Tile body: cell slots while a tile leaves room for two workgroups per CU
+//   (FP32 1024^2 16.6 against 19.1 with face slots, 2048^2 46 against 38;
+//   FP64 1024^2 22.0 against 27.0, 2048^2 83 against 75).
+// - Waves per line: at most 8 cells per lane with cell slots, 16 with face
+//   slots; FP64 lines of more than 1024 cells take two waves with two lines
+//   per workgroup (1403 x 937 40.5, 50.4 with four waves and one line) unless
+//   that loads a CU more (1200^2 49.2, 43.6) or the line is 2048 or longer
+//   (2048^2 78.9, 75.3).
+// - 3-D: FP32 cell slots and 4 lines (256^3 261, face slots 299; 200^3 142,
+//   162), the two-solve launches of the 4-step scheme 8 (293, 299); FP64 face
+//   slots (200^3 290, 312).
+// - FP32 grids of fewer than 2^18 cells, and with T = 0 walls, keep face
+//   slots and one wave per line, with two staging and storing: the two bodies
+//   and other segment lengths round differently, which on so few cells shows
+//   in the FP64 energy (234^2 with walls, 100 steps: 1e-8).  256^2 7.9 (cell
+//   slots 7.0, one staging wave 8.5, four lines per workgroup 9.1).
+inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, bool four, bool walls, SweepCfg* out) {
+    const bool keep = es == 4 && ndim == 2 && (walls || (int64_t)n * lines < (1 << 18));
+    auto units = [&](int64_t l) { return (lines + 256 * l - 1) / (256 * l) * l; };
+    int lpw = 1, wpl = 0, io = 1, body = asd::SWEEP_FACE_SLOTS;
+    for (int l = 2; l <= 16 / es; l *= 2)
+        if (3 * units(l) <= 4 * units(1)) lpw = l;
+    if (ndim == 3) {
+        if (es == 4 && n <= 512) {
+            wpl = 1;
+            if (four) lpw *= 2;
+            else body = asd::SWEEP_CELL_SLOTS;
+        }
+    } else if (keep && n <= 1024) {
+        wpl = 1;
+        io = n >= 128 ? 2 : 1;
+        lpw = std::max(lpw, io);
+    } else if (n <= (es == 8 ? 1024 : 1420)) {
+        wpl = n <= 512 ? 1 : 2;
+        body = asd::SWEEP_CELL_SLOTS;
+    } else if (es == 8) {
+        wpl = n < 2048 && units(2) == units(1) ? 2 : 4;
+        lpw = wpl == 2 ? 2 : 1;
+    } else {
+        wpl = n <= 2048 ? 2 : 4;
+    }
+    if (keep) body = asd::SWEEP_FACE_SLOTS;
+    for (; wpl > 0 && wpl <= 16; wpl *= 2)
+        if (choose_sweep_cfg_wpl(es, ndim, n, chi, wpl, lpw, out, io, body)) return true;
+    return choose_sweep_cfg(es, ndim, n, chi, 0, 0, out);
+}
+
+// Whether a 2-D sweep stores line-contiguous and transposes afterwards, and
+// its shape then.  A transposed store writes pieces of at most 16 bytes of
+// each output row; on a grid beyond the L2s they reach memory unmerged
+// (8192^2 FP32, 8-byte pieces: 4.4 bytes written per byte), the sooner if the
+// rows do not start on cache lines.  The line-contiguous store needs one line
+// per workgroup only (several workgroups per CU, whose load and solve phases
+// overlap), and the transpose costs two more passes over the state.  us per
+// step, transposed store / line-contiguous and transpose:
+//   FP32 1700^2 42 / 47, 2048^2 38 / 46, 2500^2 115 / 88, 3000^2 141 / 106,
+//   4096^2 185 / 168, 8192^2 1250 / 800; FP64 1500^2 71 / 68, 1700^2 87 / 81,
+//   2048^2 75 / 81, 2500^2 310 / 191, 4096^2 538 / 380.
+inline bool default_split(int es, int ndim, int n, int nt, bool walls, SweepCfg* out) {
+    const bool cell = es == 4 && n < 4096 && !walls;  // 3000^2 106 against 111, 4096^2 177 against 168
+    bool ok = false;
+    for (int wpl = 4; wpl <= 16 && !ok; wpl *= 2)
+        ok = choose_sweep_cfg_wpl(es, ndim, n, false, wpl, 1, out, 1, cell ? asd::SWEEP_CELL_SLOTS : asd::SWEEP_FACE_SLOTS);
+    if (!ok || ndim != 2) return false;
+    const int64_t bytes = (int64_t)n * nt * es;
+    const bool rows_aligned = ((int64_t)nt * es) % 128 == 0;
+    return bytes > (rows_aligned ? (int64_t)32 << 20 : (int64_t)16 << 20);
+}
+
 // One captured step loop, keyed on what the capture baked in.
 struct GraphEntry {
     hipGraphExec_t exec = nullptr;
@@ -162,6 +239,10 @@ struct asd_grid_s {
     unsigned* flags = nullptr;
     double* stats = nullptr;
     SweepCfg cfg[3];
+    // 2-D sweeps whose transposed store would be made of pieces too short to
+    // meet in the L2: stored line-contiguous in shape split_cfg, then transposed
+    bool split[3] = {false, false, false};
+    SweepCfg split_cfg[3];
     // graph cache of step loops: a few captured loops, least recently used
     // replaced first; graph_valid = false marks every entry stale (fields,
     // coefficients or launch shapes changed)

@@ -219,11 +219,9 @@ template <typename T>
 hipError_t launch_adjoint_stencil(const AdjParams<T>& P, hipStream_t st);
 
 // --------------------------------------------------------------- utilities
-// out[perm] = in: copy a dense (nz, ny, nx) array into another axis order.
-// dst_stride[d] is the destination stride of source axis d (x=0, y=1, z=2).
+// 2-D transpose: in [ny][nx] -> out [nx][ny].
 template <typename T>
-hipError_t launch_permute(const T* in, T* out, const int n[3], const int64_t dst_stride[3],
-                          hipStream_t st);
+hipError_t launch_transpose(const T* in, T* out, int nx, int ny, hipStream_t st);
 // Standalone FP64 reduction of a dense array of N elements (partials only).
 template <typename T>
 hipError_t launch_reduce(const T* x, int64_t N, const ReduceParams& red, int nblocks, hipStream_t st);

@@ -232,7 +232,14 @@ extern "C" int asd_batch_init(const asd_desc* descs, int32_t nprob, void* dev_ws
         b->sub[p]->stats = b->d_stats + 3 * p;
         cur += align256(wb);
     }
-    rc = batch_shape(b, 512, SWEEP_FACE_SLOTS);
+    // measured, us per step of the grouped schedule (lines of 64-512 cells):
+    // FP32, cell slots, 512 threads, capacity 8: 60 problems 58.6, 8 problems
+    // 18.3, against 66.9 and 20.8 with face slots at capacity 4; FP64, face
+    // slots, 256 threads, capacity 8: 60 problems 110, 96 problems 182,
+    // against 130 and 204 with 512 threads at capacity 4 (16 problems 36.0
+    // and 35.8)
+    rc = descs[0].dtype == ASD_F32 ? batch_shape(b, 512, SWEEP_CELL_SLOTS, 8) : batch_shape(b, 256, SWEEP_FACE_SLOTS, 8);
+    if (rc) rc = batch_shape(b, 512, SWEEP_FACE_SLOTS);
     if (rc) rc = batch_shape(b, 256, SWEEP_FACE_SLOTS);
     if (rc) {
         asd_batch_destroy(b);

@@ -40,6 +40,7 @@ extern "C" int asd_set_sweep_kernel(asd_grid g, int32_t axis, int32_t wpl, int32
         return asd_fail(ASD_EUNSUPPORTED, "launch shape wpl=%d lpw=%d io=%d variant=%d does not fit", wpl, lpw, io,
                         variant);
     g->cfg[axis] = c;
+    g->split[axis] = false;
     g->graph_valid = false;
     return ASD_OK;
 }
@@ -143,9 +144,10 @@ extern "C" int asd_bench_copy_wide(const void* src, void* dst, size_t nbytes, vo
 // ------------------------------------------------------------- autotuner
 
 // Time reps whole steps (every sweep in order, each reading what the
-// previous one wrote, as in the step loop) with the launch shapes cfg[],
-// on the two scratch buffers: the first sweep reads T, T is never written.
-static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, float* ms) {
+// previous one wrote, as in the step loop) with the launch shapes cfg[]
+// (axes with split[]: line-contiguous store and a transpose), on the two
+// scratch buffers: the first sweep reads T, T is never written.
+static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, const bool* split, float* ms) {
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return asd_fail(ASD_EHIP, "event create");
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -160,9 +162,17 @@ static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, floa
         for (int s = 0; s < steps && !rc; ++s)
             for (int d = 0; d < g->d.ndim && !rc; ++d) {
                 void* out = g->tmp[cur];
-                rc = enqueue_sweep(g, d, dt, in, out, mode, no_reduce(), &cfg[d], nullptr);
+                rc = enqueue_sweep(g, d, dt, in, out, split[d] ? mode | SWEEP_KEEP_LAYOUT : mode, no_reduce(), &cfg[d],
+                                   nullptr);
+                if (split[d] && !rc) {
+                    // back over the sweep's input, which it has read by then
+                    void* to = g->tmp[cur ^ 1];
+                    rc = enqueue_permute_2d(g, out, to, d == 0);
+                    out = to;
+                } else {
+                    cur ^= 1;
+                }
                 in = out;
-                cur ^= 1;
             }
         return rc;
     };
@@ -180,9 +190,11 @@ static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, floa
 // Autotuner: for each sweep axis in turn, every admissible (tile body,
 // waves per line, lines per workgroup, io) shape is timed inside whole steps
 // (the other axes at their current shapes), and the fastest is kept; two
-// passes.  A shape's time
-// is the best of three timings: shapes a few per cent apart are otherwise
-// ranked by the noise of a single sub-millisecond timing.
+// passes.  On 2-D grids of 16 MiB and more the line-contiguous store with a
+// transpose is tried too, in its default shape (on smaller grids the extra
+// passes cost more than short pieces of a transposed store, which meet in the
+// L2).  A shape's time is the best of three timings: shapes a few per cent
+// apart are otherwise ranked by the noise of a single sub-millisecond timing.
 extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
     if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
     if (!(std::isfinite(dt) && dt > 0.0)) return asd_fail(ASD_EINVAL, "dt must be finite and > 0");
@@ -193,11 +205,26 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
     if (rc) return rc;
     const bool chi = (g->d.flags & ASD_FLAG_PER_CELL_CHI) != 0;
     SweepCfg cur[3] = {g->cfg[0], g->cfg[1], g->cfg[2]};
+    bool split[3] = {false, false, false};
+    // FP32 with T = 0 walls stays on face slots (default_sweep_cfg has the reason)
+    const int last_body = g->es == 4 && g->d.bc == ASD_BC_DIRICHLET ? SWEEP_FACE_SLOTS : SWEEP_CELL_SLOTS;
+    const bool try_split = g->d.ndim == 2 && g->N * (int64_t)g->es >= ((int64_t)16 << 20);
+    auto best_of_three = [&](const SweepCfg* trial, const bool* sp, float* ms) {
+        *ms = 1e30f;
+        int r = ASD_OK;
+        for (int t = 0; t < 3 && !r; ++t) {
+            float one = 0.f;
+            r = time_chain(g, dt, reps, trial, sp, &one);
+            *ms = std::min(*ms, one);
+        }
+        return r;
+    };
+    SweepCfg line[3];  // the line-contiguous shapes
     for (int pass = 0; pass < 2; ++pass) {
         for (int axis = 0; axis < g->d.ndim; ++axis) {
             SweepCfg best = cur[axis];
             float best_ms = 1e30f;
-            for (int variant = SWEEP_FACE_SLOTS; variant <= SWEEP_CELL_SLOTS; ++variant)
+            for (int variant = SWEEP_FACE_SLOTS; variant <= last_body; ++variant)
             for (int io = 1; io <= (variant == SWEEP_CELL_SLOTS ? 1 : 2); ++io)
             for (int wpl = 1; wpl <= 16; wpl *= 2) {
                 for (int lpw = 1; wpl * lpw * io <= 16; lpw *= 2) {
@@ -205,15 +232,13 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
                     if (!choose_sweep_cfg((int)g->es, g->d.ndim, (int)g->d.n[axis], chi, wpl, lpw, &c, io, variant))
                         continue;
                     if (c.wpl != wpl || c.lpw != lpw || c.io != io || c.variant != variant) continue;
-                    SweepCfg trial[3] = {cur[0], cur[1], cur[2]};
+                    SweepCfg trial[3] = {split[0] ? line[0] : cur[0], split[1] ? line[1] : cur[1], cur[2]};
                     trial[axis] = c;
+                    bool sp[3] = {split[0], split[1], false};
+                    sp[axis] = false;
                     float ms = 1e30f;
-                    for (int t = 0; t < 3; ++t) {
-                        float one = 0.f;
-                        rc = time_chain(g, dt, reps, trial, &one);
-                        if (rc) return rc;
-                        ms = std::min(ms, one);
-                    }
+                    rc = best_of_three(trial, sp, &ms);
+                    if (rc) return rc;
                     if (ms < best_ms) {
                         best_ms = ms;
                         best = c;
@@ -221,9 +246,26 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
                 }
             }
             cur[axis] = best;
+            split[axis] = false;
+            if (try_split) {
+                (void)default_split((int)g->es, 2, (int)g->d.n[axis], (int)g->d.n[1 - axis],
+                                    g->d.bc == ASD_BC_DIRICHLET, &line[axis]);
+                SweepCfg trial[3] = {split[0] ? line[0] : cur[0], split[1] ? line[1] : cur[1], cur[2]};
+                trial[axis] = line[axis];
+                bool sp[3] = {split[0], split[1], false};
+                sp[axis] = true;
+                float ms = 1e30f;
+                rc = best_of_three(trial, sp, &ms);
+                if (rc) return rc;
+                split[axis] = ms < best_ms;
+            }
         }
     }
-    for (int a = 0; a < 3; ++a) g->cfg[a] = cur[a];
+    for (int a = 0; a < 3; ++a) {
+        g->cfg[a] = cur[a];
+        g->split[a] = split[a];
+        if (split[a]) g->split_cfg[a] = line[a];
+    }
     g->graph_valid = false;
     return ASD_OK;
 }

@@ -180,9 +180,12 @@ int init_grid_in_place(asd_grid_s* g, const asd_desc* desc, void* dev_ws, size_t
     g->flags = (unsigned*)sm;
     g->stats = (double*)(sm + 8);   // 3 doubles
     for (int q = 0; q < desc->ndim; ++q) {
-        if (!choose_sweep_cfg((int)g->es, desc->ndim, (int)desc->n[q],
-                              (desc->flags & ASD_FLAG_PER_CELL_CHI) != 0, 0, 0, &g->cfg[q]))
+        if (!default_sweep_cfg((int)g->es, desc->ndim, (int)desc->n[q], g->N / desc->n[q],
+                               (desc->flags & ASD_FLAG_PER_CELL_CHI) != 0, (desc->flags & ASD_FLAG_FOUR_STEP) != 0,
+                               desc->bc == ASD_BC_DIRICHLET, &g->cfg[q]))
             return asd_fail(ASD_EUNSUPPORTED, "no sweep configuration for axis %d", q);
+        g->split[q] = desc->ndim == 2 && default_split((int)g->es, 2, (int)desc->n[q], (int)desc->n[1 - q],
+                                                       desc->bc == ASD_BC_DIRICHLET, &g->split_cfg[q]);
     }
     return ASD_OK;
 }
@@ -462,13 +465,11 @@ int enqueue_sweep(asd_grid g, int d, double dt, const void* in, void* out, int r
 
 // 2-D layout change A = [y][x] -> B = [x][y] (a_to_b) or back.
 int enqueue_permute_2d(asd_grid g, const void* in, void* out, bool a_to_b) {
-    const int nx = (int)g->d.n[0], ny = (int)g->d.n[1];
-    const int n[3] = {a_to_b ? nx : ny, a_to_b ? ny : nx, 1};
-    // a B array is a dense (nx, ny) array with y fastest
-    const int64_t ds[3] = {a_to_b ? ny : nx, 1, (int64_t)nx * ny};
-    hipError_t e = g->es == 8 ? launch_permute<double>((const double*)in, (double*)out, n, ds, g->st)
-                              : launch_permute<float>((const float*)in, (float*)out, n, ds, g->st);
-    return hip_check(e, "permute launch");
+    // the input's fastest axis first
+    const int n0 = (int)g->d.n[a_to_b ? 0 : 1], n1 = (int)g->d.n[a_to_b ? 1 : 0];
+    hipError_t e = g->es == 8 ? launch_transpose<double>((const double*)in, (double*)out, n0, n1, g->st)
+                              : launch_transpose<float>((const float*)in, (float*)out, n0, n1, g->st);
+    return hip_check(e, "transpose launch");
 }
 
 // Reduce a state into the standalone slot; returns the fold that finishes it.
@@ -516,12 +517,11 @@ int check_dt(asd_grid g, double dt, bool explicit_scheme) {
 // every step's last kernel writes per-block partials into the next ring
 // slot, and one fold launch turns a full ring (or the last steps) into the
 // outputs of each of those steps, off the sweeps' critical path.
-// Workgroups of one launch of sweep d in the grid's current launch shape.
-static int64_t sweep_num_blocks(asd_grid g, int d, bool twice) {
+// Workgroups of one launch of sweep d in launch shape c.
+static int64_t sweep_num_blocks(asd_grid g, int d, SweepCfg c, bool twice) {
     const SweepGeom G = sweep_geom(g->d.ndim, d);
     const int64_t nz = g->d.ndim == 3 ? g->d.n[2] : 1;
     const int64_t nax[3] = {g->d.n[0], g->d.n[1], nz};
-    SweepCfg c = g->cfg[d];
     if (twice) (void)twice_cfg((int)g->es, g->d.ndim, (int)g->d.n[d], c, &c);
     const int lpw = c.lpw;
     return (nax[G.t1] + lpw - 1) / lpw * nax[G.t2];
@@ -542,6 +542,8 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     const bool twice = four_step_twice(g, g->cfg);
     const bool four = (g->d.flags & ASD_FLAG_FOUR_STEP) != 0 && !twice;
     const int tw = twice ? SWEEP_TWICE : 0;
+    // (two launches per direction of the 4-step scheme need both states)
+    auto split = [&](int d) { return g->split[d] && !four; };
     const bool reverse = (g->d.flags & ASD_FLAG_REVERSE_ORDER) != 0;  // 2-D only
     int rc = ASD_OK;
     // The initial state's energy: reduced by the first sweep, which reads
@@ -551,7 +553,8 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     // when the first sweep and the step's last sweep launch as many blocks,
     // the initial state's partials take ring slot 0 and are folded with the
     // first steps' (one fold launch fewer per call)
-    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0, twice) == sweep_num_blocks(g, g->d.ndim - 1, twice);
+    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0, split(0) ? g->split_cfg[0] : g->cfg[0], twice) ==
+                                           sweep_num_blocks(g, nd - 1, split(nd - 1) ? g->split_cfg[nd - 1] : g->cfg[nd - 1], twice);
     FoldParams f0{};
     bool f0_pending = false;
     if (outs.any() && !fuse_e0) {
@@ -565,7 +568,14 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     const bool chi_of_T = g->d.chi_exp != 0.0;
     auto sweep = [&](int d, const void* src, void* dst, int mode, const ReduceParams& red, int* nb) {
         int r = chi_of_T ? enqueue_coef(g, d, dt, src) : ASD_OK;
-        if (r == ASD_OK) r = enqueue_sweep(g, d, dt, src, dst, mode, red, nullptr, nb);
+        if (r == ASD_OK && split(d)) {
+            // line-contiguous into the spare state, then transposed
+            void* spare = reverse ? g->T : g->tmp[1];
+            r = enqueue_sweep(g, d, dt, src, spare, mode | SWEEP_KEEP_LAYOUT, red, &g->split_cfg[d], nb);
+            if (r == ASD_OK) r = enqueue_permute_2d(g, spare, dst, d == 0);
+        } else if (r == ASD_OK) {
+            r = enqueue_sweep(g, d, dt, src, dst, mode, red, nullptr, nb);
+        }
         return r;
     };
     int used = e0_in_ring ? 1 : 0;  // ring slots holding unfolded entries

@@ -300,8 +300,9 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
         T phi_prev = T(0), alpha_prev = T(0);
 #pragma unroll
         for (int f = 0; f <= MMAX; ++f) {
-            T phi = ca[f] * (cu[f + 1] - cu[f]) + cb1[f] * limit2<T>(lim, cs1[f + 1], cs1[f]);
-            if (NDIM == 3) phi += cb2[f] * limit2<T>(lim, cs2[f + 1], cs2[f]);
+            // (written as fma: every instantiation rounds alike)
+            T phi = fma(ca[f], cu[f + 1] - cu[f], cb1[f] * limit2<T>(lim, cs1[f + 1], cs1[f]));
+            if (NDIM == 3) phi = fma(cb2[f], limit2<T>(lim, cs2[f + 1], cs2[f]), phi);
             if (f > 0) {
                 const int i = f - 1;  // cell s0 + i, faces (f-1, f)
                 av[i] = -alpha_prev;

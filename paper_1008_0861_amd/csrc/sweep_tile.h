@@ -284,8 +284,9 @@ __device__ __forceinline__ void stage_tile(const SweepParams<T>& P, const TileCt
                         if (NDIM == 3) F += pb2 * limit2<T>(lim, last_lane ? nrs2 : rs2, ps2);
                         phi += F;
                     } else if (!solve_only) {
-                        phi += pb1 * limit2<T>(lim, last_lane ? nrs1 : rs1, ps1);
-                        if (NDIM == 3) phi += pb2 * limit2<T>(lim, last_lane ? nrs2 : rs2, ps2);
+                        // (written as fma: every instantiation rounds alike)
+                        phi = fma(pb1, limit2<T>(lim, last_lane ? nrs1 : rs1, ps1), phi);
+                        if (NDIM == 3) phi = fma(pb2, limit2<T>(lim, last_lane ? nrs2 : rs2, ps2), phi);
                     }
                     if (EXT && P.dirichlet && p == n - 1) {
                         // the wrap face couples nothing; its coefficient entry holds the

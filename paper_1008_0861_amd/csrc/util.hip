@@ -1,53 +1,44 @@
-// Small kernels of libasd: layout permutation (re-laying b and chi out so
-// that every sweep reads contiguous lines), a standalone FP64 reduction of
-// a state, fills and copies.
+// Small kernels of libasd: the 2-D transpose between the two state layouts,
+// a standalone FP64 reduction of a state, fills and copies.
 #include "asd_device.h"
 #include "asd_launch.h"
 
 namespace asd {
 
-// Tiled permutation: the block reads a 32 x 32 tile of the (y, x) plane of
-// source slice z coalesced along x and writes it coalesced along the
-// destination's fastest axis when that is y.  The general 3-D permutations
-// used here move x or y into the fastest position; z-fastest outputs are
-// written with the plane loop below.
+// 2-D transpose: in [ny][nx] -> out [nx][ny].  A block takes a 64 x 64 tile
+// through LDS (a padded row: conflict-free both ways); rows of 64 elements
+// keep every access to memory whole cache lines, and a thread's sixteen
+// loads are all in flight before the first is used.
 template <typename T>
-__global__ void __launch_bounds__(256) permute_kernel(const T* __restrict__ in, T* __restrict__ out,
-                                                     int nx, int ny, int nz, int64_t dsx, int64_t dsy,
-                                                     int64_t dsz) {
-    __shared__ T tile[32][33];
-    const int tilesx = (nx + 31) / 32, tilesy = (ny + 31) / 32;
+__global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int nx, int ny) {
+    constexpr int W = 64, R = 16;
+    __shared__ T tile[W][W + 1];
+    const int tilesx = (nx + W - 1) / W;
     int b = blockIdx.x;
-    const int tx0 = (b % tilesx) * 32;
-    b /= tilesx;
-    const int ty0 = (b % tilesy) * 32;
-    const int z = b / tilesy;
-    const int lx = threadIdx.x & 31, ly = threadIdx.x >> 5;  // 32 x 8
-    for (int r = ly; r < 32; r += 8) {
-        const int x = tx0 + lx, y = ty0 + r;
-        if (x < nx && y < ny) tile[r][lx] = in[(int64_t)x + (int64_t)y * nx + (int64_t)z * nx * ny];
+    // neighbouring tiles on one XCD (they share lines at ragged edges)
+    if ((gridDim.x & 7) == 0) b = (b & 7) * (gridDim.x >> 3) + (b >> 3);
+    const int x0 = (b % tilesx) * W, y0 = (b / tilesx) * W;
+    const int lx = threadIdx.x & 63, ly = threadIdx.x >> 6;
+    T v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int x = min(x0 + lx, nx - 1), y = min(y0 + ly + 4 * r, ny - 1);
+        v[r] = in[(int64_t)y * nx + x];
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) tile[ly + 4 * r][lx] = v[r];
     __syncthreads();
-    if (dsy == 1) {
-        // destination has y fastest: write rows of the tile transposed
-        for (int r = ly; r < 32; r += 8) {
-            const int y = ty0 + lx, x = tx0 + r;
-            if (x < nx && y < ny) out[(int64_t)x * dsx + y + (int64_t)z * dsz] = tile[lx][r];
-        }
-    } else {
-        for (int r = ly; r < 32; r += 8) {
-            const int x = tx0 + lx, y = ty0 + r;
-            if (x < nx && y < ny) out[(int64_t)x * dsx + (int64_t)y * dsy + (int64_t)z * dsz] = tile[r][lx];
-        }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int x = x0 + ly + 4 * r, y = y0 + lx;
+        if (x < nx && y < ny) out[(int64_t)x * ny + y] = tile[lx][ly + 4 * r];
     }
 }
 
 template <typename T>
-hipError_t launch_permute(const T* in, T* out, const int n[3], const int64_t ds[3], hipStream_t st) {
-    const int tilesx = (n[0] + 31) / 32, tilesy = (n[1] + 31) / 32;
-    const int64_t nb = (int64_t)tilesx * tilesy * n[2];
-    hipLaunchKernelGGL(permute_kernel<T>, dim3((unsigned)nb), dim3(256), 0, st, in, out, n[0], n[1],
-                       n[2], ds[0], ds[1], ds[2]);
+hipError_t launch_transpose(const T* in, T* out, int nx, int ny, hipStream_t st) {
+    const int64_t nb = (int64_t)((nx + 63) / 64) * ((ny + 63) / 64);
+    hipLaunchKernelGGL(transpose_kernel<T>, dim3((unsigned)nb), dim3(256), 0, st, in, out, nx, ny);
     return hipGetLastError();
 }
 
@@ -179,7 +170,7 @@ hipError_t launch_axpy(T* y, const T* x, T a, int64_t N, hipStream_t st) {
 }
 
 #define ASD_INST(T)                                                                          \
-    template hipError_t launch_permute<T>(const T*, T*, const int*, const int64_t*, hipStream_t); \
+    template hipError_t launch_transpose<T>(const T*, T*, int, int, hipStream_t);             \
     template hipError_t launch_reduce<T>(const T*, int64_t, const ReduceParams&, int, hipStream_t); \
     template hipError_t launch_copy<T>(const T*, T*, int64_t, hipStream_t);                  \
     template hipError_t launch_axpy<T>(T*, const T*, T, int64_t, hipStream_t);

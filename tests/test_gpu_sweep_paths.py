@@ -71,3 +71,31 @@ def test_a_bad_cell_spreads_over_its_line(prec, bad):
         g.T[3, 700] = bad
     assert not np.isfinite(g.run()[3]).any()
     assert g.g.status()[0] & 1
+
+
+# grids whose default sweeps store line-contiguous and transpose afterwards:
+# the transpose's ragged tiles, walls with a source, both orders, both schemes
+@pytest.mark.parametrize("prec,shape,bc,kw", [
+    ("f32", (2049, 2101), "periodic", {}),
+    ("f32", (2049, 2101), "periodic", {"reverse_order": True}),
+    ("f64", (1481, 1500), "dirichlet", {}),
+    ("f64", (1481, 1500), "insulating", {"four_step": True}),
+])
+def test_line_contiguous_store_and_transpose(prec, shape, bc, kw):
+    p = _random_problem(shape, bc, seed=9, nsteps=2)
+    if bc == "dirichlet":
+        p.src = 1.0 + 0.2 * synth.smoothed_normal(shape, 3, 4.0)
+    okw = {"reverse": True} if kw.get("reverse_order") else dict(kw)
+    ref, eref = oracle_run(p, prec, energy=True, **okw)
+    g = GpuProblem(p, prec, **kw)
+    T0 = g.T.clone()
+    got, e = g.run(energy=True)
+    err = mixed_rel_err if bc == "dirichlet" else max_rel_err
+    assert err(got, ref) <= TOL[prec]
+    np.testing.assert_allclose(e, eref, rtol=1e-12 if prec == "f64" else 1e-7, atol=0)
+    # captured and replayed: the same bits
+    g.g.set_graphs(True)
+    for _ in range(2):
+        with torch.cuda.stream(g.stream):
+            g.T.copy_(T0)
+        assert np.array_equal(g.run(), got)
