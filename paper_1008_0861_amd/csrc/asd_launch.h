@@ -145,6 +145,7 @@ struct ExplicitParams {
     const T* Q;      // source (nullptr: none): out += dtq Q
     T dtq;
     int limiter;
+    int planes;      // 3-D: planes per wave (set by launch_explicit)
     ReduceParams red;
 };
 template <typename T>

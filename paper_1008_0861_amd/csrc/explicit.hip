@@ -11,13 +11,19 @@
 // difference of a cell and its odd ghost is zero).
 //
 // gfx950 mapping: each wave owns a small block of cells, one column per
-// lane (2-D: a band of rows; 3-D: rows x planes), loads it with a one-cell
+// lane (2-D: a band of rows; 3-D: rows of consecutive planes), loads it with a one-cell
 // halo, and evaluates every face once (lane shifts across columns,
 // registers across rows and planes).  No LDS staging.
 #include "asd_device.h"
 #include "asd_launch.h"
 
 namespace asd {
+
+// What a kernel instantiation reads: a constant chi, a per-cell chi (neither
+// with T = 0 walls or a source), or any of it at run time.  The run-time
+// form's tests (and the power of chi(T)) sit between the loads of a wave's
+// block, which then wait for one another.
+enum : int { EX_CHI_CONST = 0, EX_CHI_CELL = 1, EX_GENERAL = 2 };
 
 // Neighbour coordinate with the boundary rule, in 32 bits (periodic wraps,
 // walls clamp; the odd ghost's sign is applied by the caller).
@@ -49,7 +55,7 @@ __device__ __forceinline__ T from_right(T v) { return __shfl_down(v, 1, 64); }
 template <typename T>
 __device__ __forceinline__ T from_left(T v) { return __shfl_up(v, 1, 64); }
 
-template <typename T, int LIMC>
+template <typename T, int LIMC, int MODE>
 __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T> P) {
     constexpr int TY = ExStream::TY, NR = TY + 2;  // rows y0-1 .. y0+TY
     const int nx = P.n[0], ny = P.n[1];
@@ -60,15 +66,17 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
     const int wave = blk * ExStream::WAVES + (threadIdx.x >> 6);
     const int ncb = (nx + ExStream::COLS - 1) / ExStream::COLS;
     const int nrb = (ny + TY - 1) / TY;
-    double lsum = 0.0, lmin = __builtin_huge_val(), lmax = -__builtin_huge_val();
+    double lsum = 0.0;
+    T lmin = T(__builtin_huge_val()), lmax = T(-__builtin_huge_val());
     if (wave < ncb * nrb) {  // wave-uniform
         const int cb = wave % ncb, rb = wave / ncb;
         const int x = cb * ExStream::COLS - 1 + lane;  // this lane's column (halo lanes may lie outside)
         const int y0 = rb * TY;
         const bool periodic = P.periodic != 0;
-        const bool dir = P.dirichlet != 0;
+        const bool dir = MODE == EX_GENERAL && P.dirichlet != 0;
+        const bool has_q = MODE == EX_GENERAL && P.Q != nullptr;
         const int lim = LIMC >= 0 ? LIMC : P.limiter;
-        const bool pchi = P.chi != nullptr || P.chi_exp != 0.0;
+        const bool pchi = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && (P.chi != nullptr || P.chi_exp != 0.0));
         const int xc = nb_coord32(x, nx, periodic);
         const bool xout = xc != x;
         // the band's rows: state (odd ghosts negated), b and chi
@@ -83,10 +91,10 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
             u[r] = dir && (xout != (yc != y)) ? -v : v;
             bx[r] = P.b[0][c];
             by[r] = P.b[1][c];
-            ch[r] = P.chi ? P.chi[c] : P.chi_par;
+            ch[r] = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && P.chi) ? P.chi[c] : P.chi_par;
             // chi(T): the cell's value from T^n, in FP64 (section 3.3)
-            if (P.chi_exp != 0.0) ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
-            if (r >= 1 && r <= TY && P.Q) q[r - 1] = P.Q[c];
+            if (MODE == EX_GENERAL && P.chi_exp != 0.0) ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
+            if (r >= 1 && r <= TY && has_q) q[r - 1] = P.Q[c];
         }
         const T cn0 = P.cn[0], cn1 = P.cn[1], ct01 = P.ct[0][1], ct10 = P.ct[1][0];
         const T chi_par = P.chi_par, chi_perp = P.chi_perp;
@@ -98,8 +106,8 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
             const T dpar = chif - chi_perp;
             const T alpha = cn * (chi_perp + dpar * bnf * bnf);
             const T btf = T(0.5) * (bt0 + bt1);
-            const T flux = dpar * bnf * (ct * btf * limit2<T>(lim, s1, s0));
-            return alpha * (u1 - u0) + flux;
+            // (written as fma: every instantiation rounds alike)
+            return fma(dpar * bnf, ct * btf * limit2<T>(lim, s1, s0), alpha * (u1 - u0));
         };
         // slopes along x of a row (lane shifts), along y of a row (registers)
         auto slope_x = [&](T uc) { return cell_slope<T>(lim, from_left(uc), uc, from_right(uc)); };
@@ -135,78 +143,117 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
             acc += fyh;
             if (out_col && y < ny) {
                 const T uc = u[r];
-                const T un = P.Q ? (uc + P.dtq * q[r - 1]) + acc : uc + acc;
+                const T un = has_q ? (uc + P.dtq * q[r - 1]) + acc : uc + acc;
                 P.out[(unsigned)x + (unsigned)y * (unsigned)nx] = un;
                 lsum += (double)un;
-                lmin = fmin(lmin, (double)un);
-                lmax = fmax(lmax, (double)un);
+                lmin = un < lmin ? un : lmin;
+                lmax = un > lmax ? un : lmax;
             }
             fy_low = fyh;
             sx_cur = sx_next;
         }
     }
-    if (P.red.partials) block_partials(P.red.partials, lsum, lmin, lmax);
+    if (P.red.partials) block_partials<T>(P.red.partials, lsum, lmin, lmax);
 }
 
-// 3-D: the same scheme as the 2-D streaming kernel, one wave per block of
-// 62 columns x ExStream3<T>::TY rows x ExStream3<T>::TZ planes (lane =
-// column).  A wave loads its block plus a one-cell halo on every side (all
-// loads first, in plane order), evaluates every face once (x faces by a lane
-// shift, y faces between rows and z faces between planes in registers) and
-// updates its cells.  No LDS and no barrier apart from the final reduction.
-template <typename T>
+// 3-D: the same scheme as the 2-D streaming kernel, marching along z.  A wave
+// owns 62 columns x TY rows of P.planes consecutive planes (lane = column)
+// and keeps the state, b and slopes of the current plane in registers; each
+// step loads the next plane (TY + 2 rows), evaluates every face of the current
+// plane once (x faces by a lane shift, y faces between rows, z faces between
+// planes, the lower ones kept from the step before) and updates its cells.
+// No LDS and no barrier apart from the final reduction.
+//
+// What bounds it: vector instructions (about 31 per face and 9 per slope) and
+// the L2 requests of the halo rows.  Marching loads each plane once per wave,
+// (TY + 2) / TY values per cell and field, where a 2 x 2 block of rows and
+// planes loads 4, and evaluates 3.25 faces and 4 slopes per cell instead of
+// 4 and 8 (TY = 4).  256^3 FP32: 122 us per step, 178 with 2 x 2 blocks, 199
+// with those and every option read at run time; FP64 275, 361, 393.
 struct ExStream3 {
     static constexpr int COLS = 62;
-    static constexpr int TY = 2;  // rows per wave
-    static constexpr int TZ = 2;  // planes per wave
     static constexpr int WAVES = 4;
 };
+// Rows per wave (TY): 4 in FP32 (256^3: 122 us per step, 134 with 2 rows), 2
+// in FP64, for the registers, and on grids below 2^19 cells, whose time is
+// one wave's latency (40 x 30 x 50 FP32: 8.2 against 10.2).
+template <typename T>
+static int explicit_rows(const int n[3]) {
+    return sizeof(T) == 4 && (int64_t)n[0] * n[1] * n[2] >= (1 << 19) ? 4 : 2;
+}
+// Planes per wave: long marches load fewer halo planes, short ones leave
+// more waves; the longest of 2 ... 32 that leaves 12 waves per CU.
+template <typename T>
+static int explicit_planes(const int n[3]) {
+    using S = ExStream3;
+    const int ty = explicit_rows<T>(n);
+    const int64_t cols = (int64_t)((n[0] + S::COLS - 1) / S::COLS) * ((n[1] + ty - 1) / ty);
+    int p = 32;
+    while (p > 2 && cols * ((n[2] + p - 1) / p) < 12 * 256) p /= 2;
+    return p;
+}
 
-template <typename T, int LIMC>
+// One plane of a wave's rows and their halo rows.
+template <typename T, int NR>
+struct ExPlane {
+    T u[NR], bx[NR], by[NR], bz[NR], ch[NR];
+    T sx[NR], sy[NR];  // limited slopes along x, and along y (inner rows)
+};
+
+template <typename T, int LIMC, int MODE, int TY>
 __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T> P) {
-    using S = ExStream3<T>;
-    constexpr int TY = S::TY, TZ = S::TZ, NR = TY + 2, NP = TZ + 2;
+    using S = ExStream3;
+    constexpr int NR = TY + 2;
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     const int lane = threadIdx.x & 63;
     const int blk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);  // XCD-aware order
-    const int wave = blk * S::WAVES + (threadIdx.x >> 6);
-    const int ncb = (nx + S::COLS - 1) / S::COLS, nrb = (ny + TY - 1) / TY, nzb = (nz + TZ - 1) / TZ;
-    double lsum = 0.0, lmin = __builtin_huge_val(), lmax = -__builtin_huge_val();
+    // wave-uniform (readfirstlane): the row and plane arithmetic stays scalar
+    const int wave = blk * S::WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int ncb = (nx + S::COLS - 1) / S::COLS, nrb = (ny + TY - 1) / TY, nzb = (nz + P.planes - 1) / P.planes;
+    double lsum = 0.0;
+    T lmin = T(__builtin_huge_val()), lmax = T(-__builtin_huge_val());
     if (wave < ncb * nrb * nzb) {  // wave-uniform
         const int cb = wave % ncb, rb = (wave / ncb) % nrb, zb = wave / (ncb * nrb);
         const int x = cb * S::COLS - 1 + lane;
-        const int y0 = rb * TY, z0 = zb * TZ;
+        const int y0 = rb * TY, z0 = zb * P.planes;
+        const int z1 = min(z0 + P.planes, nz);
         const bool periodic = P.periodic != 0;
-        const bool dir = P.dirichlet != 0;
+        const bool dir = MODE == EX_GENERAL && P.dirichlet != 0;
+        const bool has_q = MODE == EX_GENERAL && P.Q != nullptr;
         const int lim = LIMC >= 0 ? LIMC : P.limiter;
-        const bool pchi = P.chi != nullptr || P.chi_exp != 0.0;
+        const bool pchi = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && (P.chi != nullptr || P.chi_exp != 0.0));
         const int xc = nb_coord32(x, nx, periodic);
         const bool xout = xc != x;
         const unsigned sy = (unsigned)nx, sz = (unsigned)nx * (unsigned)ny;
-        // the block and its halo: plane q is z0-1+q, row r is y0-1+r
-        T u[NP][NR], bx[NP][NR], by[NP][NR], bz[NP][NR], ch[NP][NR], q[TZ][TY];
-#pragma unroll
-        for (int pq = 0; pq < NP; ++pq) {
-            const int z = z0 - 1 + pq;
+        using Plane = ExPlane<T, NR>;
+        // plane z of the wave's rows y0-1 .. y0+TY, all loads before any use
+        auto load = [&](int z, Plane& p) {
             const int zc = nb_coord32(z, nz, periodic);
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
                 const int y = y0 - 1 + r;
+                // (rows past ny, in the last block, are clamped to a valid one and not stored)
                 const int yc = nb_coord32(y, ny, periodic);
                 const unsigned c = (unsigned)xc + (unsigned)yc * sy + (unsigned)zc * sz;
                 const T v = P.U[c];
                 // odd ghost: one sign flip per axis on which the cell lies outside
                 const int nout = (int)xout + (int)(yc != y) + (int)(zc != z);
-                u[pq][r] = dir && (nout & 1) ? -v : v;
-                bx[pq][r] = P.b[0][c];
-                by[pq][r] = P.b[1][c];
-                bz[pq][r] = P.b[2][c];
-                ch[pq][r] = P.chi ? P.chi[c] : P.chi_par;
+                p.u[r] = dir && (nout & 1) ? -v : v;
+                p.bx[r] = P.b[0][c];
+                p.by[r] = P.b[1][c];
+                p.bz[r] = P.b[2][c];
+                p.ch[r] = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && P.chi) ? P.chi[c] : P.chi_par;
                 // chi(T): the cell's value from T^n, in FP64 (section 3.3)
-                if (P.chi_exp != 0.0) ch[pq][r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
-                if (P.Q && pq >= 1 && pq <= TZ && r >= 1 && r <= TY) q[pq - 1][r - 1] = P.Q[c];
+                if (MODE == EX_GENERAL && P.chi_exp != 0.0) p.ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
             }
-        }
+        };
+        auto slopes = [&](Plane& p) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                p.sx[r] = cell_slope<T>(lim, from_left(p.u[r]), p.u[r], from_right(p.u[r]));
+                p.sy[r] = (r >= 1 && r <= TY) ? cell_slope<T>(lim, p.u[r - 1], p.u[r], p.u[r + 1]) : T(0);
+            }
+        };
         const T chi_par = P.chi_par, chi_perp = P.chi_perp;
         // face between cells 0 and 1 along the normal axis n; a and b are the
         // two transverse axes in increasing order (components ta, tb of b,
@@ -220,82 +267,92 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
             T tr = T(0);
             tr += cta * (T(0.5) * (ta0 + ta1)) * limit2<T>(lim, sa1, sa0);
             tr += ctb * (T(0.5) * (tb0 + tb1)) * limit2<T>(lim, sb1, sb0);
-            const T flux = dpar * bnf * tr;
-            return alpha * (u1 - u0) + flux;
+            // (written as fma: every instantiation rounds alike)
+            return fma(dpar * bnf, tr, alpha * (u1 - u0));
         };
-        // limited slopes: along x for every loaded cell (lane shifts), along
-        // y for the inner rows, along z for the inner planes
-        T sxs[NP][NR], sys[NP][NR], szs[NP][NR];
-#pragma unroll
-        for (int pq = 0; pq < NP; ++pq) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                sxs[pq][r] = cell_slope<T>(lim, from_left(u[pq][r]), u[pq][r], from_right(u[pq][r]));
-                sys[pq][r] = (r >= 1 && r <= TY) ? cell_slope<T>(lim, u[pq][r - 1], u[pq][r], u[pq][r + 1]) : T(0);
-                szs[pq][r] = (pq >= 1 && pq <= TZ) ? cell_slope<T>(lim, u[pq - 1][r], u[pq][r], u[pq + 1][r]) : T(0);
-            }
-        }
         const bool xwall = !periodic && !dir && (x < 0 || x + 1 > nx - 1);
         const bool out_col = lane >= 1 && lane <= S::COLS && x < nx;
-        // lower z faces of the first plane
-        T fz_lo[TY];
-        {
-            const bool zwall = !periodic && !dir && (z0 - 1 < 0 || z0 > nz - 1);
+        auto zfaces = [&](int z, const Plane& a, const Plane& b, T (&f)[TY]) {  // between planes z and z + 1
+            const bool zwall = !periodic && !dir && (z < 0 || z + 1 > nz - 1);
 #pragma unroll
             for (int r = 1; r <= TY; ++r) {
-                const T f = face(u[0][r], u[1][r], bz[0][r], bz[1][r], bx[0][r], bx[1][r], by[0][r], by[1][r], ch[0][r],
-                                 ch[1][r], sxs[0][r], sxs[1][r], sys[0][r], sys[1][r], P.cn[2], P.ct[2][0], P.ct[2][1]);
-                fz_lo[r - 1] = zwall ? T(0) : f;
+                const T v = face(a.u[r], b.u[r], a.bz[r], b.bz[r], a.bx[r], b.bx[r], a.by[r], b.by[r], a.ch[r], b.ch[r],
+                                 a.sx[r], b.sx[r], a.sy[r], b.sy[r], P.cn[2], P.ct[2][0], P.ct[2][1]);
+                f[r - 1] = zwall ? T(0) : v;
             }
-        }
+        };
+        T up[NR];     // the state of the plane below
+        Plane C;      // the current plane
+        T fz_lo[TY];  // its lower z faces
+        {
+            Plane B;
+            load(z0 - 1, B);
+            load(z0, C);
+            slopes(B);
+            slopes(C);
+            zfaces(z0 - 1, B, C, fz_lo);
 #pragma unroll
-        for (int pq = 1; pq <= TZ; ++pq) {
-            const int z = z0 - 1 + pq;
+            for (int r = 0; r < NR; ++r) up[r] = B.u[r];
+        }
+#pragma unroll 1
+        for (int z = z0; z < z1; ++z) {
+            Plane N;
+            load(z + 1, N);
+            T q[TY];
+            if (has_q) {
+#pragma unroll
+                for (int r = 1; r <= TY; ++r)
+                    q[r - 1] = P.Q[(unsigned)xc + (unsigned)min(y0 - 1 + r, ny - 1) * sy + (unsigned)z * sz];
+            }
+            slopes(N);
+            T szs[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) szs[r] = cell_slope<T>(lim, up[r], C.u[r], N.u[r]);
             // y faces of this plane, rows r and r+1, r = 0 .. TY
             T fy[TY + 1];
 #pragma unroll
             for (int r = 0; r <= TY; ++r) {
                 const int y = y0 - 1 + r;
                 const bool ywall = !periodic && !dir && (y < 0 || y + 1 > ny - 1);
-                const T f = face(u[pq][r], u[pq][r + 1], by[pq][r], by[pq][r + 1], bx[pq][r], bx[pq][r + 1], bz[pq][r],
-                                 bz[pq][r + 1], ch[pq][r], ch[pq][r + 1], sxs[pq][r], sxs[pq][r + 1], szs[pq][r],
-                                 szs[pq][r + 1], P.cn[1], P.ct[1][0], P.ct[1][2]);
+                const T f = face(C.u[r], C.u[r + 1], C.by[r], C.by[r + 1], C.bx[r], C.bx[r + 1], C.bz[r], C.bz[r + 1],
+                                 C.ch[r], C.ch[r + 1], C.sx[r], C.sx[r + 1], szs[r], szs[r + 1], P.cn[1], P.ct[1][0],
+                                 P.ct[1][2]);
                 fy[r] = ywall ? T(0) : f;
             }
-            const bool zwall = !periodic && !dir && (z < 0 || z + 1 > nz - 1);
+            T fz_hi[TY];
+            zfaces(z, C, N, fz_hi);
 #pragma unroll
             for (int r = 1; r <= TY; ++r) {
                 const int y = y0 - 1 + r;
-                T fxr = face(u[pq][r], from_right(u[pq][r]), bx[pq][r], from_right(bx[pq][r]), by[pq][r],
-                             from_right(by[pq][r]), bz[pq][r], from_right(bz[pq][r]), ch[pq][r], from_right(ch[pq][r]),
-                             sys[pq][r], from_right(sys[pq][r]), szs[pq][r], from_right(szs[pq][r]), P.cn[0],
-                             P.ct[0][1], P.ct[0][2]);
+                T fxr = face(C.u[r], from_right(C.u[r]), C.bx[r], from_right(C.bx[r]), C.by[r], from_right(C.by[r]),
+                             C.bz[r], from_right(C.bz[r]), C.ch[r], pchi ? from_right(C.ch[r]) : C.ch[r], C.sy[r],
+                             from_right(C.sy[r]), szs[r], from_right(szs[r]), P.cn[0], P.ct[0][1], P.ct[0][2]);
                 fxr = xwall ? T(0) : fxr;
                 const T fxl = from_left(fxr);
-                T fzh = face(u[pq][r], u[pq + 1][r], bz[pq][r], bz[pq + 1][r], bx[pq][r], bx[pq + 1][r], by[pq][r],
-                             by[pq + 1][r], ch[pq][r], ch[pq + 1][r], sxs[pq][r], sxs[pq + 1][r], sys[pq][r],
-                             sys[pq + 1][r], P.cn[2], P.ct[2][0], P.ct[2][1]);
-                fzh = zwall ? T(0) : fzh;
                 T acc = T(0);
                 acc += -fxl;
                 acc += fxr;
                 acc += -fy[r - 1];
                 acc += fy[r];
                 acc += -fz_lo[r - 1];
-                acc += fzh;
-                if (out_col && y < ny && z < nz) {
-                    const T uc = u[pq][r];
-                    const T un = P.Q ? (uc + P.dtq * q[pq - 1][r - 1]) + acc : uc + acc;
+                acc += fz_hi[r - 1];
+                if (out_col && y < ny) {
+                    const T uc = C.u[r];
+                    const T un = has_q ? (uc + P.dtq * q[r - 1]) + acc : uc + acc;
                     P.out[(unsigned)x + (unsigned)y * sy + (unsigned)z * sz] = un;
                     lsum += (double)un;
-                    lmin = fmin(lmin, (double)un);
-                    lmax = fmax(lmax, (double)un);
+                    lmin = un < lmin ? un : lmin;
+                    lmax = un > lmax ? un : lmax;
                 }
-                fz_lo[r - 1] = fzh;
             }
+#pragma unroll
+            for (int r = 0; r < NR; ++r) up[r] = C.u[r];
+#pragma unroll
+            for (int r = 0; r < TY; ++r) fz_lo[r] = fz_hi[r];
+            C = N;
         }
     }
-    if (P.red.partials) block_partials(P.red.partials, lsum, lmin, lmax);
+    if (P.red.partials) block_partials<T>(P.red.partials, lsum, lmin, lmax);
 }
 
 // Blocks of an explicit launch: a multiple of 8 for the XCD-aware order.
@@ -306,8 +363,9 @@ static int explicit_blocks_t(int ndim, const int n[3]) {
         waves = ((n[0] + ExStream::COLS - 1) / ExStream::COLS) * ((n[1] + ExStream::TY - 1) / ExStream::TY);
         per_block = ExStream::WAVES;
     } else {
-        using S = ExStream3<T>;
-        waves = ((n[0] + S::COLS - 1) / S::COLS) * ((n[1] + S::TY - 1) / S::TY) * ((n[2] + S::TZ - 1) / S::TZ);
+        using S = ExStream3;
+        const int pl = explicit_planes<T>(n), ty = explicit_rows<T>(n);
+        waves = ((n[0] + S::COLS - 1) / S::COLS) * ((n[1] + ty - 1) / ty) * ((n[2] + pl - 1) / pl);
         per_block = S::WAVES;
     }
     const int blocks = (waves + per_block - 1) / per_block;
@@ -321,19 +379,31 @@ int explicit_num_blocks(int ndim, const int n[3]) {
 }
 
 template <typename T>
-hipError_t launch_explicit(const ExplicitParams<T>& P, int ndim, hipStream_t st, int* nblocks_out) {
+hipError_t launch_explicit(const ExplicitParams<T>& Pin, int ndim, hipStream_t st, int* nblocks_out) {
+    ExplicitParams<T> P = Pin;
+    P.planes = ndim == 3 ? explicit_planes<T>(P.n) : 1;
     const int nb = explicit_blocks_t<T>(ndim, P.n);
     if (nblocks_out) *nblocks_out = nb;
     const bool vl = P.limiter == LIM_VANLEER;
+    const int mode = P.dirichlet || P.Q || P.chi_exp != 0.0 ? EX_GENERAL : P.chi ? EX_CHI_CELL : EX_CHI_CONST;
+#define ASD_EXPLICIT_LAUNCH(KERNEL, NT, ...)                                                                     \
+    do {                                                                                                         \
+        if (!vl) hipLaunchKernelGGL((KERNEL<T, -1, EX_GENERAL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P);      \
+        else if (mode == EX_GENERAL) hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_GENERAL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
+        else if (mode == EX_CHI_CELL) hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_CHI_CELL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
+        else hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_CHI_CONST __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
+    } while (0)
+#define ASD_COMMA ,
     if (ndim == 2) {
-        constexpr int NT = 64 * ExStream::WAVES;
-        if (vl) hipLaunchKernelGGL((explicit_stream2d_kernel<T, LIM_VANLEER>), dim3(nb), dim3(NT), 0, st, P);
-        else hipLaunchKernelGGL((explicit_stream2d_kernel<T, -1>), dim3(nb), dim3(NT), 0, st, P);
+        ASD_EXPLICIT_LAUNCH(explicit_stream2d_kernel, 64 * ExStream::WAVES, );
+    } else if constexpr (sizeof(T) == 4) {
+        if (explicit_rows<T>(P.n) == 4) ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 4);
+        else ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 2);
     } else {
-        constexpr int NT = 64 * ExStream3<T>::WAVES;
-        if (vl) hipLaunchKernelGGL((explicit_stream3d_kernel<T, LIM_VANLEER>), dim3(nb), dim3(NT), 0, st, P);
-        else hipLaunchKernelGGL((explicit_stream3d_kernel<T, -1>), dim3(nb), dim3(NT), 0, st, P);
+        ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 2);
     }
+#undef ASD_COMMA
+#undef ASD_EXPLICIT_LAUNCH
     return hipGetLastError();
 }
 
