@@ -197,6 +197,17 @@ int asd_adjoint_step_stored(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_
                             const void *dev_lambda_final, void *dev_grad_T0, void *dev_grad_chi,
                             void *dev_adj_ws, size_t adj_ws_bytes);
 
+/* The same pair for a caller that keeps the whole workspace, untouched,
+ * between the two: when nsteps <= 2 ckpt_every the forward also leaves every
+ * state in it (in the fields the recomputation would fill), and the reverse
+ * pass recomputes none.  Same workspace size, results and errors; the two
+ * pairs do not mix. */
+int asd_adjoint_forward_states(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every, void *dev_adj_ws,
+                               size_t adj_ws_bytes);
+int asd_adjoint_step_states(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every,
+                            const void *dev_lambda_final, void *dev_grad_T0, void *dev_grad_chi,
+                            void *dev_adj_ws, size_t adj_ws_bytes);
+
 /* Synchronise the grid's stream and report status flags (ASD_STATUS_*)
  * from an FP64 reduction of the current T; stats (nullable, 3 doubles)
  * receives {sum T dV, min T, max T}. */

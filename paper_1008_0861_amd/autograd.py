@@ -1,8 +1,9 @@
 """torch.autograd.Function over the C ABI: nsteps semi-implicit steps as a
-differentiable map (T0, chi) -> T_N.  The forward runs asd_adjoint_forward
-(the steps, storing a checkpoint every ckpt_every steps); the backward is the
-hand-written adjoint asd_adjoint_step_stored, which recomputes each segment
-from its stored checkpoint."""
+differentiable map (T0, chi) -> T_N.  The forward runs
+asd_adjoint_forward_states (the steps, storing a checkpoint every ckpt_every
+steps, or every state when there are at most two segments); the backward is
+the hand-written adjoint asd_adjoint_step_states, which recomputes each
+segment that was not stored from its checkpoint."""
 import torch
 
 from . import binding
@@ -25,10 +26,10 @@ class SemiImplicitSteps(torch.autograd.Function):
             grid.set_field("chi", chi_c)
             T = T0.detach().clone()
             grid.set_field("T", T)
-            ws = grid.adjoint_forward(dt, nsteps, ckpt_every)
+            ws = grid.adjoint_forward(dt, nsteps, ckpt_every, states=True)
         cur.wait_stream(grid.stream)
         ctx.save_for_backward(chi_c)
-        ctx.ws = ws  # the checkpoints (states at steps 0, k, 2k, ...)
+        ctx.ws = ws  # the checkpoints (states at steps 0, k, 2k, ...), or all states
         ctx.grid, ctx.dt, ctx.nsteps, ctx.k = grid, dt, nsteps, ckpt_every
         return T
 
@@ -40,7 +41,8 @@ class SemiImplicitSteps(torch.autograd.Function):
         grid.stream.wait_stream(cur)
         with torch.cuda.stream(grid.stream):
             grid.set_field("chi", chi)
-            gT0, gchi = grid.adjoint_stored(ctx.dt, ctx.nsteps, ctx.k, ctx.ws, gT.contiguous(), grad_chi=True)
+            gT0, gchi = grid.adjoint_stored(ctx.dt, ctx.nsteps, ctx.k, ctx.ws, gT.contiguous(), grad_chi=True,
+                                            states=True)
         cur.wait_stream(grid.stream)
         ctx.ws = None
         return gT0, gchi, None, None, None, None

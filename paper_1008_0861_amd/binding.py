@@ -34,7 +34,8 @@ GRAPHS_OFF, GRAPHS_AUTO, GRAPHS_ALWAYS = 0, 1, 2
 EXPORTED = [
     "asd_last_error", "asd_workspace_bytes", "asd_init_grid", "asd_set_field",
     "asd_step_semi_implicit", "asd_step_explicit_limited", "asd_step_series", "asd_adjoint_workspace_bytes",
-    "asd_adjoint_step", "asd_adjoint_forward", "asd_adjoint_step_stored", "asd_status", "asd_destroy",
+    "asd_adjoint_step", "asd_adjoint_forward", "asd_adjoint_step_stored", "asd_adjoint_forward_states",
+    "asd_adjoint_step_states", "asd_status", "asd_destroy",
     "asd_batch_workspace_bytes", "asd_batch_init", "asd_batch_set_problem", "asd_batch_step",
     "asd_batch_destroy", "asd_batch_set_block", "asd_batch_set_variant", "asd_batch_get_variant", "asd_batch_tune",
     "asd_batch_set_capacity",
@@ -96,6 +97,8 @@ def lib():
             "asd_adjoint_step": (ctypes.c_int, [vp, dbl, i32, i32, vp, vp, vp, vp, vp, sz]),
             "asd_adjoint_forward": (ctypes.c_int, [vp, dbl, i32, i32, vp, sz]),
             "asd_adjoint_step_stored": (ctypes.c_int, [vp, dbl, i32, i32, vp, vp, vp, vp, sz]),
+            "asd_adjoint_forward_states": (ctypes.c_int, [vp, dbl, i32, i32, vp, sz]),
+            "asd_adjoint_step_states": (ctypes.c_int, [vp, dbl, i32, i32, vp, vp, vp, vp, sz]),
             "asd_status": (ctypes.c_int, [vp, P(ctypes.c_uint32), P(dbl)]),
             "asd_destroy": (ctypes.c_int, [vp]),
             "asd_batch_workspace_bytes": (ctypes.c_int, [P(Desc), i32, P(sz)]),
@@ -300,24 +303,25 @@ class Grid:
         check(lib().asd_adjoint_workspace_bytes(self.handle, int(nsteps), int(ckpt_every), ctypes.byref(n)))
         return torch.empty(max(n.value, 1), dtype=torch.uint8, device=self.device)
 
-    def adjoint_forward(self, dt, nsteps, ckpt_every, ws=None):
+    def adjoint_forward(self, dt, nsteps, ckpt_every, ws=None, states=False):
         """nsteps semi-implicit steps of T in place, storing the reverse
-        pass's checkpoints in ws (allocated if None); returns ws."""
+        pass's checkpoints in ws (allocated if None); returns ws.  states:
+        every state where ws holds them (for adjoint_stored with states)."""
         if ws is None:
             ws = self.adjoint_workspace(nsteps, ckpt_every)
-        check(lib().asd_adjoint_forward(self.handle, float(dt), int(nsteps), int(ckpt_every),
-                                        ctypes.c_void_p(ws.data_ptr()), ws.numel()))
+        f = lib().asd_adjoint_forward_states if states else lib().asd_adjoint_forward
+        check(f(self.handle, float(dt), int(nsteps), int(ckpt_every), ctypes.c_void_p(ws.data_ptr()), ws.numel()))
         return ws
 
-    def adjoint_stored(self, dt, nsteps, ckpt_every, ws, lam, grad_chi=True):
-        """dL/dT0 (and dL/dchi) from the checkpoints adjoint_forward left in ws."""
+    def adjoint_stored(self, dt, nsteps, ckpt_every, ws, lam, grad_chi=True, states=False):
+        """dL/dT0 (and dL/dchi) from what adjoint_forward (with the same states) left in ws."""
         self._check_tensor(lam)
         gT = torch.empty_like(lam)
         gC = torch.empty_like(lam) if grad_chi else None
-        check(lib().asd_adjoint_step_stored(self.handle, float(dt), int(nsteps), int(ckpt_every),
-                                            ctypes.c_void_p(lam.data_ptr()), ctypes.c_void_p(gT.data_ptr()),
-                                            ctypes.c_void_p(gC.data_ptr()) if gC is not None else None,
-                                            ctypes.c_void_p(ws.data_ptr()), ws.numel()))
+        f = lib().asd_adjoint_step_states if states else lib().asd_adjoint_step_stored
+        check(f(self.handle, float(dt), int(nsteps), int(ckpt_every), ctypes.c_void_p(lam.data_ptr()),
+                ctypes.c_void_p(gT.data_ptr()), ctypes.c_void_p(gC.data_ptr()) if gC is not None else None,
+                ctypes.c_void_p(ws.data_ptr()), ws.numel()))
         return gT, gC
 
     def sweep_config(self, axis):

@@ -31,6 +31,12 @@ struct AdjPlan {
     size_t total;
 };
 
+// With one or two segments the state sets hold every state of the call, so
+// the forward stores them all and the reverse pass recomputes nothing.  (With
+// more, the reverse pass reuses the sets for earlier segments, and a second
+// reverse pass from the same workspace has to find what the first one found.)
+static bool keeps_all_states(const AdjPlan& p) { return p.nck <= 2; }
+
 static AdjPlan adj_plan(asd_grid g, int nsteps, int k) {
     AdjPlan p{};
     p.k = k;
@@ -42,6 +48,34 @@ static AdjPlan adj_plan(asd_grid g, int nsteps, int k) {
     p.total = p.field * ((size_t)p.nck + (size_t)(2 * k * p.nbuf) + 4);
     return p;
 }
+
+// The workspace's fields, in order.
+struct AdjBufs {
+    std::vector<void*> ck;             // checkpoints
+    std::vector<void*> S[2], TS[2];    // per set: states T^{ck k + i} (i >= 1), T* of each step
+    void *tB, *lam, *lamB, *mu;
+    AdjBufs(const AdjPlan& pl, char* ws) {
+        auto take = [&]() {
+            char* p = ws;
+            ws += pl.field;
+            return (void*)p;
+        };
+        ck.resize(pl.nck);
+        for (int c = 0; c < pl.nck; ++c) ck[c] = take();
+        for (int s = 0; s < pl.nbuf; ++s) {
+            S[s].assign(pl.k + 1, nullptr);
+            for (int i = 1; i <= pl.k; ++i) S[s][i] = take();
+        }
+        for (int s = 0; s < pl.nbuf; ++s) {
+            TS[s].assign(pl.k, nullptr);
+            for (int i = 0; i < pl.k; ++i) TS[s][i] = take();
+        }
+        tB = take();
+        lam = take();   // lambda* (after a y sweep's reverse), layout A
+        lamB = take();  // lambda^n (after an x sweep's reverse), layout B: the y solve's input
+        mu = take();
+    }
+};
 
 // The second stream and the events of the overlapped reverse pass, created
 // on a grid's first adjoint call with several segments (default priority,
@@ -129,23 +163,32 @@ static int stencil(asd_grid g, int d, double dt, const void* mu, const void* U, 
 // states at steps 0, k, 2k, ... written to the workspace's checkpoint
 // fields (the y sweep of a checkpoint step writes there directly and the
 // next step reads it there).  The last step always ends in T.
-static int forward_ckpt(asd_grid g, double dt, int nsteps, int k, char* ws) {
+//
+// states: with one or two segments every state goes into the sets (the y sweeps write
+// there, the x sweeps store T* a second time in the stencils' layout, and the
+// last state is copied), in the workspace that the recomputation would fill:
+// 1024^2 FP64, 20 steps, checkpoints every 10, forward and backward 2090 ->
+// 1700 us.
+static int forward_ckpt(asd_grid g, double dt, int nsteps, int k, char* ws, bool states) {
     const AdjPlan pl = adj_plan(g, nsteps, k);
-    auto ck = [&](int c) { return (void*)(ws + (size_t)c * pl.field); };
-    int rc = enqueue_copy(g, g->T, ck(0));
+    const AdjBufs B(pl, ws);
+    const bool all = states && keeps_all_states(pl);
+    int rc = enqueue_copy(g, g->T, B.ck[0]);
     const void* in = g->T;
     for (int s = 0; s < nsteps && rc == ASD_OK; ++s) {
-        rc = enqueue_sweep(g, 0, dt, in, g->tmp[0], 0, no_reduce(), nullptr, nullptr);
+        const int c = s / k, i = s % k, set = c & 1;
+        rc = enqueue_sweep(g, 0, dt, in, g->tmp[0], 0, no_reduce(), nullptr, nullptr, all ? B.TS[set][i] : nullptr);
         if (rc) break;
-        const int c = (s + 1) / k;
-        void* out = ((s + 1) % k == 0 && c < pl.nck) ? ck(c) : g->T;
+        void* out = i + 1 == k && c + 1 < pl.nck ? B.ck[c + 1] : all ? B.S[set][i + 1] : g->T;
         rc = enqueue_sweep(g, 1, dt, g->tmp[0], out, 0, no_reduce(), nullptr, nullptr);
         in = out;
     }
+    if (rc == ASD_OK && in != g->T) rc = enqueue_copy(g, in, g->T);
     return rc;
 }
 
 // stored: the checkpoints are already in ws (asd_adjoint_forward); T0 unused.
+// states: so are, with one or two segments, all states (asd_adjoint_forward_states).
 //
 // With several segments the recomputation of segment c-1 (on the grid's
 // second stream) overlaps the reverse pass over segment c (on the grid's
@@ -155,29 +198,11 @@ static int forward_ckpt(asd_grid g, double dt, int nsteps, int k, char* ws) {
 //   1 + s: state set s has been recomputed,  3 + s: set s has been consumed.
 template <typename T>
 static int adjoint_t(asd_grid g, double dt, int nsteps, int k, const void* T0, const void* lamN, void* gT0,
-                     void* gchi, char* ws, bool stored) {
+                     void* gchi, char* ws, bool stored, bool states) {
     const AdjPlan pl = adj_plan(g, nsteps, k);
-    char* cur = ws;
-    auto take = [&]() {
-        char* p = cur;
-        cur += pl.field;
-        return (void*)p;
-    };
-    std::vector<void*> ck(pl.nck);
-    for (int c = 0; c < pl.nck; ++c) ck[c] = take();
-    std::vector<void*> S[2], TS[2];  // per set: recomputed states T^{ck k + i} (i >= 1), T* of each step
-    for (int s = 0; s < pl.nbuf; ++s) {
-        S[s].assign(k + 1, nullptr);
-        for (int i = 1; i <= k; ++i) S[s][i] = take();
-    }
-    for (int s = 0; s < pl.nbuf; ++s) {
-        TS[s].assign(k, nullptr);
-        for (int i = 0; i < k; ++i) TS[s][i] = take();
-    }
-    void* tB = take();
-    void* lam = take();   // lambda* (after a y sweep's reverse), layout A
-    void* lamB = take();  // lambda^n (after an x sweep's reverse), layout B: the y solve's input
-    void* mu = take();
+    const AdjBufs B(pl, ws);
+    const std::vector<void*>&ck = B.ck, *S = B.S, *TS = B.TS;
+    void *const tB = B.tB, *const lam = B.lam, *const lamB = B.lamB, *const mu = B.mu;
     int rc = ASD_OK;
     // forward pass: checkpoints at steps 0, k, 2k, ...
     if (!stored) rc = enqueue_copy(g, T0, ck[0]);
@@ -242,7 +267,9 @@ static int adjoint_t(asd_grid g, double dt, int nsteps, int k, const void* T0, c
         return ASD_OK;
     };
     const int last = pl.nck - 1;
-    if (pl.nbuf == 1) {
+    if (states && keeps_all_states(pl)) {
+        for (int c = last; c >= 0 && rc == ASD_OK; --c) rc = reverse(c, c & 1);
+    } else if (pl.nbuf == 1) {
         rc = recompute(0, 0);
         if (rc == ASD_OK) rc = reverse(0, 0);
     } else {
@@ -310,26 +337,42 @@ extern "C" int asd_adjoint_step(asd_grid g, double dt, int32_t nsteps, int32_t c
     int rc = adj_validate(g, dt, nsteps, ckpt_every, dev_grad_chi != nullptr, dev_adj_ws, adj_ws_bytes);
     if (rc) return rc;
     return g->es == 8 ? adjoint_t<double>(g, dt, nsteps, ckpt_every, dev_T0, dev_lambda_final, dev_grad_T0,
-                                          dev_grad_chi, (char*)dev_adj_ws, false)
+                                          dev_grad_chi, (char*)dev_adj_ws, false, false)
                       : adjoint_t<float>(g, dt, nsteps, ckpt_every, dev_T0, dev_lambda_final, dev_grad_T0,
-                                         dev_grad_chi, (char*)dev_adj_ws, false);
+                                         dev_grad_chi, (char*)dev_adj_ws, false, false);
+}
+
+static int forward_call(asd_grid g, double dt, int nsteps, int k, void* ws, size_t ws_bytes, bool states) {
+    int rc = adj_validate(g, dt, nsteps, k, false, ws, ws_bytes);
+    if (rc) return rc;
+    return forward_ckpt(g, dt, nsteps, k, (char*)ws, states);
+}
+static int reverse_call(asd_grid g, double dt, int nsteps, int k, const void* lam, void* gT0, void* gchi, void* ws,
+                        size_t ws_bytes, bool states) {
+    if (g && (!lam || !gT0)) return asd_fail(ASD_EINVAL, "NULL state pointer");
+    int rc = adj_validate(g, dt, nsteps, k, gchi != nullptr, ws, ws_bytes);
+    if (rc) return rc;
+    return g->es == 8 ? adjoint_t<double>(g, dt, nsteps, k, nullptr, lam, gT0, gchi, (char*)ws, true, states)
+                      : adjoint_t<float>(g, dt, nsteps, k, nullptr, lam, gT0, gchi, (char*)ws, true, states);
 }
 
 extern "C" int asd_adjoint_forward(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every, void* dev_adj_ws,
                                    size_t adj_ws_bytes) {
-    int rc = adj_validate(g, dt, nsteps, ckpt_every, false, dev_adj_ws, adj_ws_bytes);
-    if (rc) return rc;
-    return forward_ckpt(g, dt, nsteps, ckpt_every, (char*)dev_adj_ws);
+    return forward_call(g, dt, nsteps, ckpt_every, dev_adj_ws, adj_ws_bytes, false);
 }
-
 extern "C" int asd_adjoint_step_stored(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every,
                                        const void* dev_lambda_final, void* dev_grad_T0, void* dev_grad_chi,
                                        void* dev_adj_ws, size_t adj_ws_bytes) {
-    if (g && (!dev_lambda_final || !dev_grad_T0)) return asd_fail(ASD_EINVAL, "NULL state pointer");
-    int rc = adj_validate(g, dt, nsteps, ckpt_every, dev_grad_chi != nullptr, dev_adj_ws, adj_ws_bytes);
-    if (rc) return rc;
-    return g->es == 8 ? adjoint_t<double>(g, dt, nsteps, ckpt_every, nullptr, dev_lambda_final, dev_grad_T0,
-                                          dev_grad_chi, (char*)dev_adj_ws, true)
-                      : adjoint_t<float>(g, dt, nsteps, ckpt_every, nullptr, dev_lambda_final, dev_grad_T0,
-                                         dev_grad_chi, (char*)dev_adj_ws, true);
+    return reverse_call(g, dt, nsteps, ckpt_every, dev_lambda_final, dev_grad_T0, dev_grad_chi, dev_adj_ws,
+                        adj_ws_bytes, false);
+}
+extern "C" int asd_adjoint_forward_states(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every, void* dev_adj_ws,
+                                          size_t adj_ws_bytes) {
+    return forward_call(g, dt, nsteps, ckpt_every, dev_adj_ws, adj_ws_bytes, true);
+}
+extern "C" int asd_adjoint_step_states(asd_grid g, double dt, int32_t nsteps, int32_t ckpt_every,
+                                       const void* dev_lambda_final, void* dev_grad_T0, void* dev_grad_chi,
+                                       void* dev_adj_ws, size_t adj_ws_bytes) {
+    return reverse_call(g, dt, nsteps, ckpt_every, dev_lambda_final, dev_grad_T0, dev_grad_chi, dev_adj_ws,
+                        adj_ws_bytes, true);
 }
