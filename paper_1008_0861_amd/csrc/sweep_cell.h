@@ -507,8 +507,18 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
     lsum = 0.0;
     lmin = T(__builtin_huge_val());
     lmax = T(-__builtin_huge_val());
+    // Which word of its slot a solution takes.  All words are dead by now
+    // (one or two waves per line: the last exchange went through its own
+    // buffer), and with U's word for all a wave's accesses would fall into a
+    // quarter of the banks.  Aligned tiles spread them over the four words, by
+    // line and by the segment's row of lanes (1024^2 FP32 16.6 -> 16.0 us per
+    // step, 512^2 9.85 -> 9.2).
+    const bool spread = FULL && P.wpl <= 2;
+    constexpr int M_LOG2 = MMAX >= 16 ? 4 : MMAX >= 8 ? 3 : MMAX >= 4 ? 2 : MMAX >= 2 ? 1 : 0;
+    auto xword = [&](int line, int p) { return spread ? ((line + (p >> (M_LOG2 + wpl_log2))) & 3) * ES : UPOS; };
     if (active) {
         T dn = XR;
+        const int xw = xword(q, s0);
 #pragma unroll
         for (int i = MMAX - 1; i >= 0; --i) {
             if (i < m) {
@@ -516,7 +526,7 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
                 if (i < MMAX - 1 && i != m - 1) d = gv[i] - hv[i] * dn + wv[i] * XL;
                 dn = d;
                 const T x = cu[i + 1] + d;
-                *reinterpret_cast<T*>(row1 + os0 + i * SLOT + UPOS) = x;
+                *reinterpret_cast<T*>(row1 + os0 + i * SLOT + xw) = x;
                 const T rv = red_in ? cu[i + 1] : x;
                 lsum += (double)rv;
                 lmin = rv < lmin ? rv : lmin;
@@ -540,8 +550,9 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
         // second copy in the input layout (EXT instantiations only): lpw runs
         // of consecutive cells per store
         T* ob2 = EXT && P.out2 && qq_ok ? P.out2 + (unsigned)((l1_0 + qq) * P.si_t1 + l2 * P.si_t2) : nullptr;
-        // pstep == spl: consecutive positions of a thread are ostep1 apart in LDS
-        const unsigned char* rq = ctx.buf + qq * Lo.row1 + UPOS + cell_off1(p0, ES, pad);
+        // pstep == spl: consecutive positions of a thread are ostep1 apart in
+        // LDS, at the same word (spl is a multiple of four segments per wave)
+        const unsigned char* rq = ctx.buf + qq * Lo.row1 + xword(qq, p0) + cell_off1(p0, ES, pad);
         const unsigned o0 = (unsigned)(p0 * P.so_n + qq);
         const unsigned ostep = (unsigned)(pstep * P.so_n);
 #pragma unroll
@@ -565,7 +576,7 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
         for (int it = 0; it < MMAX; ++it) {
             const int p = k + (it << spl_log2);
             if (p >= n) break;
-            ob[(unsigned)(p * P.so_n)] = *reinterpret_cast<const T*>(row1 + ok1 + it * ostep1 + UPOS);
+            ob[(unsigned)(p * P.so_n)] = *reinterpret_cast<const T*>(row1 + ok1 + it * ostep1 + xword(q, k));
         }
     }
 
