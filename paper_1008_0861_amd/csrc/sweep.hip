@@ -62,7 +62,8 @@ __global__ void __launch_bounds__((SweepBounds<T, MMAX>::max_threads))
 }
 
 // The 4-step scheme's two solves of a direction in one launch: one pass over
-// memory instead of two (256^3 FP32, tuned shapes: 427 -> 293 us per step).
+// memory instead of two (256^3 FP32: 427 -> 305 us per step, 293 with 8
+// lines per workgroup).
 template <typename T, int NDIM, int MMAX, int LIMC, bool EXT>
 __global__ void __launch_bounds__((sweep_twice_max_threads((int)sizeof(T), MMAX)))
     sweep_twice_kernel(const T* U, const T* alpha, const T* beta1, int n, int nt1, int si_t1, int si_t2, int nb1,
@@ -107,9 +108,9 @@ __global__ void __launch_bounds__((SweepCellBounds<T, MMAX>::max_threads))
 // Van Leer, minmod and MC get straight-line instantiations of their own; the
 // linear mean reads the limiter at run time.  T = 0 walls, a source or a
 // second output take the EXT instantiations, van Leer's or the run-time one.
-// (A limiter read at run time costs several branches per face: 129^2 FP64
-// with walls and a source, van Leer, 7.1 us per sweep; see the launcher's
-// users for the straight-line times.)
+// (A limiter read at run time costs several branches per face: 1403 x 937
+// FP32 MC 386 us per 10 steps, 345 straight-line; 129^2 FP64 with walls and a
+// source, van Leer, 1492 and 1389 us per 100 steps.)
 template <typename T, int NDIM>
 hipError_t launch_sweep_dim(const SweepParams<T>& P, int mmax, dim3 grid, dim3 block, size_t lds, hipStream_t st,
                             int variant) {
