@@ -179,34 +179,53 @@ __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     if (partials) block_partials<T>(partials, lsum, lmin, lmax);
 }
 
-// Block p: FP64 energy of problem p's current state (its x-sweep input).
+// The FP64 energies of the problems' current states (their x-sweep inputs),
+// in two launches: block (p, c) sums slice c of problem p into the first
+// entries of the problem's y-sweep partials (ring slot 0, free until the first
+// y sweep), then block p adds its slices in order.  One block per problem read
+// 512^2 FP32 at what one CU keeps in flight, 26-30 us; the slices share it out.
+static constexpr int kReduce0Slices = 16;
 template <typename T>
-__global__ void __launch_bounds__(1024) batch_reduce0_kernel(const BatchProblem<T>* probs, BatchOut out) {
+__device__ __forceinline__ int reduce0_slices(const BatchProblem<T>& bp) {
+    return bp.ngroups[1] < kReduce0Slices ? bp.ngroups[1] : kReduce0Slices;
+}
+template <typename T>
+__global__ void __launch_bounds__(256) batch_reduce0_kernel(const BatchProblem<T>* probs, BatchOut out) {
     const BatchProblem<T>& bp = probs[blockIdx.x];
+    const int S = reduce0_slices(bp), c = blockIdx.y;
+    if (c >= S) return;  // block-uniform
     const SweepParams<T>& P = bp.sweep[0];
-    const int N = P.n * P.nt1;
-    // one block per problem: bound by the latency of its rounds of loads, so
-    // sixteen are in flight per thread (four partial sums, combined in a
-    // fixed order); with four, 512^2 FP32 took 30 us
-    constexpr int U = 16;
+    const int64_t N = (int64_t)P.n * P.nt1;
+    const int i1 = (int)(N * (c + 1) / S);
+    constexpr int U = 8;  // loads in flight per thread
     double s4[4] = {0.0, 0.0, 0.0, 0.0};
     T mn = T(__builtin_huge_val()), mx = T(-__builtin_huge_val());
     const int nth = (int)blockDim.x;
-    for (int i0 = threadIdx.x; i0 < N; i0 += nth * U) {
+    for (int i0 = (int)(N * c / S) + (int)threadIdx.x; i0 < i1; i0 += nth * U) {
         T v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = P.U[i0 + u * nth < N ? i0 + u * nth : i0];
+        for (int u = 0; u < U; ++u) v[u] = P.U[i0 + u * nth < i1 ? i0 + u * nth : i0];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            s4[u & 3] += i0 + u * nth < N ? (double)v[u] : 0.0;
+            s4[u & 3] += i0 + u * nth < i1 ? (double)v[u] : 0.0;
             mn = v[u] < mn ? v[u] : mn;
             mx = v[u] > mx ? v[u] : mx;
         }
     }
     const double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    double S, MN, MX;
-    block_reduce3<T>(s, mn, mx, S, MN, MX);
-    if (threadIdx.x == 0) out.energy[(size_t)blockIdx.x * out.stride] = S * bp.dV;
+    double E, MN, MX;
+    block_reduce3<T>(s, mn, mx, E, MN, MX);
+    if (threadIdx.x == 0) out.partials[3 * ((size_t)bp.tile0 + c)] = E;
+}
+template <typename T>
+__global__ void __launch_bounds__(64) batch_fold0_kernel(const BatchProblem<T>* probs, int nprob, BatchOut out) {
+    const int p = blockIdx.x * 64 + threadIdx.x;
+    if (p >= nprob) return;
+    const BatchProblem<T>& bp = probs[p];
+    const int S = reduce0_slices(bp);
+    double E = 0.0;
+    for (int c = 0; c < S; ++c) E += out.partials[3 * ((size_t)bp.tile0 + c)];
+    out.energy[(size_t)p * out.stride] = E * bp.dV;
 }
 
 // Block (p, c): fold ring slot c of the y-sweep partials of problem p into
@@ -353,7 +372,10 @@ hipError_t launch_batch_grouped(const BatchProblem<T>* probs, const int* group_s
 }
 template <typename T>
 hipError_t launch_batch_reduce0(const BatchProblem<T>* probs, int nprob, const BatchOut& out, hipStream_t st) {
-    hipLaunchKernelGGL(batch_reduce0_kernel<T>, dim3(nprob), dim3(1024), 0, st, probs, out);
+    hipLaunchKernelGGL(batch_reduce0_kernel<T>, dim3(nprob, kReduce0Slices), dim3(256), 0, st, probs, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(batch_fold0_kernel<T>, dim3((nprob + 63) / 64), dim3(64), 0, st, probs, nprob, out);
     return hipGetLastError();
 }
 
