@@ -14,16 +14,25 @@
 // lane (2-D: a band of rows; 3-D: rows of consecutive planes), loads it with a one-cell
 // halo, and evaluates every face once (lane shifts across columns,
 // registers across rows and planes).  No LDS staging.
+#include <algorithm>
+
 #include "asd_device.h"
 #include "asd_launch.h"
 
 namespace asd {
 
-// What a kernel instantiation reads: a constant chi, a per-cell chi (neither
-// with T = 0 walls or a source), or any of it at run time.  The run-time
-// form's tests (and the power of chi(T)) sit between the loads of a wave's
-// block, which then wait for one another.
-enum : int { EX_CHI_CONST = 0, EX_CHI_CELL = 1, EX_GENERAL = 2 };
+// What a kernel instantiation reads (MODE): a constant chi, a per-cell chi or
+// chi(T), and with EX_EXTRA also T = 0 walls and a source, told apart at run
+// time.  Every limiter has its own instantiations too: tests of the mode or the
+// limiter inside a wave's block keep its loads and faces waiting for one
+// another (256^3 FP32, us per step: minmod 271-312 with both read at run time,
+// 110 straight-line; van Leer with walls 159 and 112).
+enum : int { EX_CHI_CONST = 0, EX_CHI_CELL = 1, EX_CHI_OF_T = 2, EX_EXTRA = 4 };
+template <int MODE>
+struct ExMode {
+    static constexpr int chi = MODE & 3;
+    static constexpr bool extra = (MODE & EX_EXTRA) != 0;
+};
 
 // Neighbour coordinate with the boundary rule, in 32 bits (periodic wraps,
 // walls clamp; the odd ghost's sign is applied by the caller).
@@ -55,7 +64,7 @@ __device__ __forceinline__ T from_right(T v) { return __shfl_down(v, 1, 64); }
 template <typename T>
 __device__ __forceinline__ T from_left(T v) { return __shfl_up(v, 1, 64); }
 
-template <typename T, int LIMC, int MODE>
+template <typename T, int LIM, int MODE>
 __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T> P) {
     constexpr int TY = ExStream::TY, NR = TY + 2;  // rows y0-1 .. y0+TY
     const int nx = P.n[0], ny = P.n[1];
@@ -73,10 +82,10 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
         const int x = cb * ExStream::COLS - 1 + lane;  // this lane's column (halo lanes may lie outside)
         const int y0 = rb * TY;
         const bool periodic = P.periodic != 0;
-        const bool dir = MODE == EX_GENERAL && P.dirichlet != 0;
-        const bool has_q = MODE == EX_GENERAL && P.Q != nullptr;
-        const int lim = LIMC >= 0 ? LIMC : P.limiter;
-        const bool pchi = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && (P.chi != nullptr || P.chi_exp != 0.0));
+        const bool dir = ExMode<MODE>::extra && P.dirichlet != 0;
+        const bool has_q = ExMode<MODE>::extra && P.Q != nullptr;
+        constexpr int lim = LIM;
+        constexpr bool pchi = ExMode<MODE>::chi != EX_CHI_CONST;
         const int xc = nb_coord32(x, nx, periodic);
         const bool xout = xc != x;
         // the band's rows: state (odd ghosts negated), b and chi
@@ -91,9 +100,9 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
             u[r] = dir && (xout != (yc != y)) ? -v : v;
             bx[r] = P.b[0][c];
             by[r] = P.b[1][c];
-            ch[r] = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && P.chi) ? P.chi[c] : P.chi_par;
+            ch[r] = ExMode<MODE>::chi == EX_CHI_CELL ? P.chi[c] : P.chi_par;
             // chi(T): the cell's value from T^n, in FP64 (section 3.3)
-            if (MODE == EX_GENERAL && P.chi_exp != 0.0) ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
+            if (ExMode<MODE>::chi == EX_CHI_OF_T) ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
             if (r >= 1 && r <= TY && has_q) q[r - 1] = P.Q[c];
         }
         const T cn0 = P.cn[0], cn1 = P.cn[1], ct01 = P.ct[0][1], ct10 = P.ct[1][0];
@@ -168,28 +177,44 @@ __global__ void __launch_bounds__(256) explicit_stream2d_kernel(ExplicitParams<T
 // the L2 requests of the halo rows.  Marching loads each plane once per wave,
 // (TY + 2) / TY values per cell and field, where a 2 x 2 block of rows and
 // planes loads 4, and evaluates 3.25 faces and 4 slopes per cell instead of
-// 4 and 8 (TY = 4).  256^3 FP32: 122 us per step, 178 with 2 x 2 blocks, 199
-// with those and every option read at run time; FP64 275, 361, 393.
+// 4 and 8 (TY = 4).  256^3, us per step without energies: FP32 110, 2 x 2
+// blocks with every option read at run time 140; FP64 245 and 330.
 struct ExStream3 {
     static constexpr int COLS = 62;
     static constexpr int WAVES = 4;
 };
-// Rows per wave (TY): 4 in FP32 (256^3: 122 us per step, 134 with 2 rows), 2
-// in FP64, for the registers, and on grids below 2^19 cells, whose time is
-// one wave's latency (40 x 30 x 50 FP32: 8.2 against 10.2).
+// Rows per wave (TY): 4 in FP32 on grids of 2^21 cells and more (us per step
+// with 4 and 2 rows: 256^3 107-113 and 111, 200^3 51 and 62, 140^3 23.6 and
+// 24.5), 2 on smaller ones (100^3 12.1 and 10.9, 256 x 30 x 256 17.9 and 17.2)
+// and in FP64, for the registers.
 template <typename T>
 static int explicit_rows(const int n[3]) {
-    return sizeof(T) == 4 && (int64_t)n[0] * n[1] * n[2] >= (1 << 19) ? 4 : 2;
+    return sizeof(T) == 4 && (int64_t)n[0] * n[1] * n[2] >= (1 << 21) ? 4 : 2;
 }
 // Planes per wave: long marches load fewer halo planes, short ones leave
-// more waves; the longest of 2 ... 32 that leaves 12 waves per CU.
+// more waves; the longest of 2 ... 32 that leaves 12 waves per CU.  With chi(T)
+// the power of every loaded cell is most of the work, and the time is that of
+// the SIMD with the most waves: the march with the least of waves per SIMD times
+// loaded planes (one wave alone counts for 1.4, it hides little of its latency).
+// us per step, chi(T): 80^3 FP64 43.7 with 2 planes, 39.7 with 4, 45.6 with 8;
+// 100^3 FP64 59.7, 58.8, 68.6, 54.9 with 6; 200^3 FP32 182 with 8, 210 with 16.
 template <typename T>
-static int explicit_planes(const int n[3]) {
+static int explicit_planes(const int n[3], bool of_T) {
     using S = ExStream3;
     const int ty = explicit_rows<T>(n);
     const int64_t cols = (int64_t)((n[0] + S::COLS - 1) / S::COLS) * ((n[1] + ty - 1) / ty);
+    auto waves = [&](int p) { return cols * ((n[2] + p - 1) / p); };
     int p = 32;
-    while (p > 2 && cols * ((n[2] + p - 1) / p) < 12 * 256) p /= 2;
+    if (of_T) {
+        auto cost = [&](int q) {
+            const int64_t k = (waves(q) + 1023) / 1024;
+            return (double)(q + 2) * (k == 1 ? 1.4 : (double)k);
+        };
+        for (int q = 31; q >= 1; --q)
+            if (cost(q) < cost(p)) p = q;
+    } else {
+        while (p > 2 && waves(p) < 12 * 256) p /= 2;
+    }
     return p;
 }
 
@@ -200,7 +225,7 @@ struct ExPlane {
     T sx[NR], sy[NR];  // limited slopes along x, and along y (inner rows)
 };
 
-template <typename T, int LIMC, int MODE, int TY>
+template <typename T, int LIM, int MODE, int TY>
 __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T> P) {
     using S = ExStream3;
     constexpr int NR = TY + 2;
@@ -218,10 +243,10 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
         const int y0 = rb * TY, z0 = zb * P.planes;
         const int z1 = min(z0 + P.planes, nz);
         const bool periodic = P.periodic != 0;
-        const bool dir = MODE == EX_GENERAL && P.dirichlet != 0;
-        const bool has_q = MODE == EX_GENERAL && P.Q != nullptr;
-        const int lim = LIMC >= 0 ? LIMC : P.limiter;
-        const bool pchi = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && (P.chi != nullptr || P.chi_exp != 0.0));
+        const bool dir = ExMode<MODE>::extra && P.dirichlet != 0;
+        const bool has_q = ExMode<MODE>::extra && P.Q != nullptr;
+        constexpr int lim = LIM;
+        constexpr bool pchi = ExMode<MODE>::chi != EX_CHI_CONST;
         const int xc = nb_coord32(x, nx, periodic);
         const bool xout = xc != x;
         const unsigned sy = (unsigned)nx, sz = (unsigned)nx * (unsigned)ny;
@@ -242,9 +267,15 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
                 p.bx[r] = P.b[0][c];
                 p.by[r] = P.b[1][c];
                 p.bz[r] = P.b[2][c];
-                p.ch[r] = MODE == EX_CHI_CELL || (MODE == EX_GENERAL && P.chi) ? P.chi[c] : P.chi_par;
-                // chi(T): the cell's value from T^n, in FP64 (section 3.3)
-                if (MODE == EX_GENERAL && P.chi_exp != 0.0) p.ch[r] = (T)((double)P.chi_par * pow((double)v / P.chi_tref, P.chi_exp));
+                // (chi(T): T^n, until chi_of_T)
+                p.ch[r] = ExMode<MODE>::chi == EX_CHI_CELL ? P.chi[c] : ExMode<MODE>::chi == EX_CHI_OF_T ? v : P.chi_par;
+            }
+        };
+        // chi(T): the cells' values from T^n, in FP64 (section 3.3)
+        auto chi_of_T = [&](Plane& p) {
+            if constexpr (ExMode<MODE>::chi == EX_CHI_OF_T) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) p.ch[r] = (T)((double)P.chi_par * pow((double)p.ch[r] / P.chi_tref, P.chi_exp));
             }
         };
         auto slopes = [&](Plane& p) {
@@ -290,6 +321,8 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
             load(z0, C);
             slopes(B);
             slopes(C);
+            chi_of_T(B);
+            chi_of_T(C);
             zfaces(z0 - 1, B, C, fz_lo);
 #pragma unroll
             for (int r = 0; r < NR; ++r) up[r] = B.u[r];
@@ -319,6 +352,7 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
                                  P.ct[1][2]);
                 fy[r] = ywall ? T(0) : f;
             }
+            chi_of_T(N);
             T fz_hi[TY];
             zfaces(z, C, N, fz_hi);
 #pragma unroll
@@ -357,14 +391,14 @@ __global__ void __launch_bounds__(256) explicit_stream3d_kernel(ExplicitParams<T
 
 // Blocks of an explicit launch: a multiple of 8 for the XCD-aware order.
 template <typename T>
-static int explicit_blocks_t(int ndim, const int n[3]) {
+static int explicit_blocks_t(int ndim, const int n[3], bool of_T) {
     int waves, per_block;
     if (ndim == 2) {
         waves = ((n[0] + ExStream::COLS - 1) / ExStream::COLS) * ((n[1] + ExStream::TY - 1) / ExStream::TY);
         per_block = ExStream::WAVES;
     } else {
         using S = ExStream3;
-        const int pl = explicit_planes<T>(n), ty = explicit_rows<T>(n);
+        const int pl = explicit_planes<T>(n, of_T), ty = explicit_rows<T>(n);
         waves = ((n[0] + S::COLS - 1) / S::COLS) * ((n[1] + ty - 1) / ty) * ((n[2] + pl - 1) / pl);
         per_block = S::WAVES;
     }
@@ -372,38 +406,53 @@ static int explicit_blocks_t(int ndim, const int n[3]) {
     return (blocks + 7) & ~7;
 }
 
-// The larger of the two precisions' block counts (sizes the reduction scratch).
+// The larger of the two precisions' block counts (sizes the reduction
+// scratch), with and without chi(T).
 int explicit_num_blocks(int ndim, const int n[3]) {
-    const int a = explicit_blocks_t<float>(ndim, n), b = explicit_blocks_t<double>(ndim, n);
-    return a > b ? a : b;
+    int most = 0;
+    for (bool of_T : {false, true}) {
+        most = std::max(most, explicit_blocks_t<float>(ndim, n, of_T));
+        most = std::max(most, explicit_blocks_t<double>(ndim, n, of_T));
+    }
+    return most;
+}
+
+template <typename T, int LIM, int MODE>
+static void launch_instance(const ExplicitParams<T>& P, int ndim, int nb, hipStream_t st) {
+    constexpr int MOST = sizeof(T) == 4 ? 4 : 2;  // rows of the 3-D instantiations: 2, and 4 in FP32
+    if (ndim == 2)
+        hipLaunchKernelGGL((explicit_stream2d_kernel<T, LIM, MODE>), dim3(nb), dim3(64 * ExStream::WAVES), 0, st, P);
+    else if (explicit_rows<T>(P.n) == MOST)
+        hipLaunchKernelGGL((explicit_stream3d_kernel<T, LIM, MODE, MOST>), dim3(nb), dim3(64 * ExStream3::WAVES), 0, st, P);
+    else
+        hipLaunchKernelGGL((explicit_stream3d_kernel<T, LIM, MODE, 2>), dim3(nb), dim3(64 * ExStream3::WAVES), 0, st, P);
+}
+template <typename T, int LIM, int CHI>
+static void launch_mode(const ExplicitParams<T>& P, int ndim, int nb, hipStream_t st) {
+    if (P.dirichlet || P.Q) launch_instance<T, LIM, CHI | EX_EXTRA>(P, ndim, nb, st);
+    else launch_instance<T, LIM, CHI>(P, ndim, nb, st);
+}
+template <typename T, int LIM>
+static void launch_limiter(const ExplicitParams<T>& P, int ndim, int nb, hipStream_t st) {
+    if (P.chi_exp != 0.0) launch_mode<T, LIM, EX_CHI_OF_T>(P, ndim, nb, st);
+    else if (P.chi) launch_mode<T, LIM, EX_CHI_CELL>(P, ndim, nb, st);
+    else launch_mode<T, LIM, EX_CHI_CONST>(P, ndim, nb, st);
 }
 
 template <typename T>
 hipError_t launch_explicit(const ExplicitParams<T>& Pin, int ndim, hipStream_t st, int* nblocks_out) {
     ExplicitParams<T> P = Pin;
-    P.planes = ndim == 3 ? explicit_planes<T>(P.n) : 1;
-    const int nb = explicit_blocks_t<T>(ndim, P.n);
+    const bool of_T = P.chi_exp != 0.0;
+    P.planes = ndim == 3 ? explicit_planes<T>(P.n, of_T) : 1;
+    const int nb = explicit_blocks_t<T>(ndim, P.n, of_T);
     if (nblocks_out) *nblocks_out = nb;
-    const bool vl = P.limiter == LIM_VANLEER;
-    const int mode = P.dirichlet || P.Q || P.chi_exp != 0.0 ? EX_GENERAL : P.chi ? EX_CHI_CELL : EX_CHI_CONST;
-#define ASD_EXPLICIT_LAUNCH(KERNEL, NT, ...)                                                                     \
-    do {                                                                                                         \
-        if (!vl) hipLaunchKernelGGL((KERNEL<T, -1, EX_GENERAL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P);      \
-        else if (mode == EX_GENERAL) hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_GENERAL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
-        else if (mode == EX_CHI_CELL) hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_CHI_CELL __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
-        else hipLaunchKernelGGL((KERNEL<T, LIM_VANLEER, EX_CHI_CONST __VA_ARGS__>), dim3(nb), dim3(NT), 0, st, P); \
-    } while (0)
-#define ASD_COMMA ,
-    if (ndim == 2) {
-        ASD_EXPLICIT_LAUNCH(explicit_stream2d_kernel, 64 * ExStream::WAVES, );
-    } else if constexpr (sizeof(T) == 4) {
-        if (explicit_rows<T>(P.n) == 4) ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 4);
-        else ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 2);
-    } else {
-        ASD_EXPLICIT_LAUNCH(explicit_stream3d_kernel, 64 * ExStream3::WAVES, ASD_COMMA 2);
+    switch (P.limiter) {
+        case LIM_VANLEER: launch_limiter<T, LIM_VANLEER>(P, ndim, nb, st); break;
+        case LIM_MINMOD: launch_limiter<T, LIM_MINMOD>(P, ndim, nb, st); break;
+        case LIM_MC: launch_limiter<T, LIM_MC>(P, ndim, nb, st); break;
+        case LIM_LINEAR: launch_limiter<T, LIM_LINEAR>(P, ndim, nb, st); break;
+        default: return hipErrorInvalidValue;
     }
-#undef ASD_COMMA
-#undef ASD_EXPLICIT_LAUNCH
     return hipGetLastError();
 }
 
