@@ -54,23 +54,34 @@ __device__ __forceinline__ FaceCoef face_coef(const CoefParams<T>& C, int i, int
     return f;
 }
 
-// x sweep: the output has the input's layout, one thread per cell.
-template <typename T>
-__global__ void __launch_bounds__(256) coef_x_kernel(CoefParams<T> C) {
-    const int nx = C.n[0];
-    const int chunks = (nx + 255) / 256;
-    const int64_t total = (int64_t)chunks * C.n[1] * C.n[2];
-    // (grids of very many short rows have more chunks than a launch takes)
-    for (int64_t b = blockIdx.x; b < total; b += gridDim.x) {
-        const int row = (int)(b / chunks);  // y + z ny
-        const int x = (int)(b - (int64_t)row * chunks) * 256 + (int)threadIdx.x;
-        if (x >= nx) continue;
-        const bool last = x + 1 == nx;
-        const int i = row * nx + x, j = last ? row * nx : i + 1;
-        const FaceCoef f = face_coef<T>(C, i, j, last && !C.periodic, coef_cell_chi<T>(C, i, i), coef_cell_chi<T>(C, j, j));
-        C.alpha[i] = (T)f.a;
-        C.beta1[i] = (T)f.b1;
-        if (C.ndim == 3) C.beta2[i] = (T)f.b2;
+// One thread per cell: the x sweep, whose output has the input's layout, and
+// the other sweeps of small and thin grids (coef_by_cells), written to the
+// output layout directly.
+template <typename T, bool X>
+__global__ void __launch_bounds__(256) coef_cell_kernel(CoefParams<T> C) {
+    const int nx = C.n[0], ny = C.n[1], nz = C.n[2];
+    const int N = nx * ny * nz;
+    // 64-bit loop index: the stride would overflow int near N = 2^31 (each i < N fits an int)
+    for (int64_t i64 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i64 < N; i64 += (int64_t)gridDim.x * blockDim.x) {
+        const int i = (int)i64, x = i % nx;
+        int j, o, oj;  // the next cell, and both in the output layout
+        bool last;
+        if constexpr (X) {
+            last = x + 1 == nx;
+            o = i;
+            oj = j = last ? i - x : i + 1;
+        } else {
+            const int c[3] = {x, (i / nx) % ny, i / (nx * ny)};
+            const int back = C.n[C.d] - 1, st = C.d == 1 ? nx : nx * ny;
+            last = c[C.d] == back;
+            o = x * C.so[0] + c[1] * C.so[1] + c[2] * C.so[2];
+            j = last ? i - back * st : i + st;
+            oj = last ? o - back : o + 1;
+        }
+        const FaceCoef f = face_coef<T>(C, i, j, last && !C.periodic, coef_cell_chi<T>(C, i, o), coef_cell_chi<T>(C, j, oj));
+        C.alpha[o] = (T)f.a;
+        C.beta1[o] = (T)f.b1;
+        if (C.ndim == 3) C.beta2[o] = (T)f.b2;
     }
 }
 
@@ -130,13 +141,27 @@ __global__ void __launch_bounds__(256) coef_t_kernel(CoefParams<T> C) {
     }
 }
 
+// The y and z sweeps' tiles need enough of them to fill the chip, more so with
+// chi(T), whose power takes longest.  us per one-step call that computes the
+// coefficients, cells / tiles: 256^2 FP32 15.1 / 16.1, 400^2 21.2 / 21.0, 64^3
+// with a per-cell chi 36.5 / 39.0, 80^3 67.7 / 54.8; chi(T), us per step: 256^2 17.6 / 24.9, 600^2 39.1 / 41.7, 64^3
+// 45.3 / 54.4, 80^3 81.2 / 78.8.  Short lines and chi(T), 300 x 300 x 4: 86 / 124,
+// x 12 FP32 157 / 173, FP64 235 / 211; rows shorter than half a tile, 8 x 400 x 400:
+// 159 / 315.  (A thread per cell of a row in chunks of 256, as the x sweep once
+// had, idles on short rows: 64 x 300 x 300 FP32 329, 294 by cells.)
+static bool coef_by_cells(int es, int ndim, int d, const int n[3], bool of_T) {
+    const int64_t N = (int64_t)n[0] * n[1] * n[2];
+    return d == 0 || N <= (of_T ? 1 << 19 : ndim == 3 ? 1 << 18 : 1 << 17) || n[0] < 16 || (of_T && n[d] <= 48 / es);
+}
+
 template <typename T>
 hipError_t launch_coef(const CoefParams<T>& C, hipStream_t st) {
     if (C.so[C.d] != 1) return hipErrorInvalidValue;  // the sweep's input layout: its axis fastest
-    if (C.d == 0) {
-        if (C.so[1] != C.n[0] || (C.ndim == 3 && C.so[2] != C.n[0] * C.n[1])) return hipErrorInvalidValue;
-        const int64_t nb = std::min<int64_t>((int64_t)((C.n[0] + 255) / 256) * C.n[1] * C.n[2], 1 << 20);
-        hipLaunchKernelGGL(coef_x_kernel<T>, dim3((unsigned)nb), dim3(256), 0, st, C);
+    if (C.d == 0 && (C.so[1] != C.n[0] || (C.ndim == 3 && C.so[2] != C.n[0] * C.n[1]))) return hipErrorInvalidValue;
+    if (coef_by_cells((int)sizeof(T), C.ndim, C.d, C.n, C.U != nullptr)) {
+        const int64_t nb = std::min<int64_t>(((int64_t)C.n[0] * C.n[1] * C.n[2] + 255) / 256, 16384);
+        if (C.d == 0) hipLaunchKernelGGL((coef_cell_kernel<T, true>), dim3((unsigned)nb), dim3(256), 0, st, C);
+        else hipLaunchKernelGGL((coef_cell_kernel<T, false>), dim3((unsigned)nb), dim3(256), 0, st, C);
     } else {
         const int w = C.ndim == 3 ? 3 - C.d : 2;
         const int64_t nb = (int64_t)((C.n[0] + 31) / 32) * ((C.n[C.d] + 31) / 32) * C.n[w];
