@@ -386,7 +386,7 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
             Ra = T(0); Rc = T(0); Rd = T(0);
         }
         if constexpr (FULL) pcr_wave64<T>(wrow, Ra, Rc, Rd);
-        else pcr_lanes<T>(k & 63, nseg, Ra, Rc, Rd);
+        else pcr_lanes<T, 64>(k & 63, nseg, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         XL = __shfl(XR, row_lane(wrow - 1), 64);
     } else {
@@ -491,7 +491,7 @@ __device__ __forceinline__ void cell_solve_store(const SweepParams<T>& P, const 
         }
         // strides wpl and up: partners are rows of this wave, s / wpl apart
         if constexpr (FULL) pcr_wave64<T>(wrow, Ra, Rc, Rd);
-        else pcr_lanes<T>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
+        else pcr_lanes<T, 64>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         cur ^= 1;
         *reinterpret_cast<T*>(slot(cur, kseg)) = XR;

@@ -501,7 +501,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
             Ra = T(0); Rc = T(0); Rd = T(0);
         }
         if constexpr (ROWS) pcr_wave64<T>(wrow, Ra, Rc, Rd);
-        else pcr_lanes<T>((int)threadIdx.x & 63, nseg, Ra, Rc, Rd);
+        else pcr_lanes<T, LPL>((int)threadIdx.x & 63, nseg, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         XL = __shfl(XR, row_lane(wrow - 1), 64);
     } else {
@@ -606,7 +606,7 @@ __device__ __forceinline__ void solve_store(const SweepParams<T>& P, const TileC
         }
         // strides wpl and up: partners are rows of this wave, s / wpl apart
         if constexpr (ROWS) pcr_wave64<T>(wrow, Ra, Rc, Rd);
-        else pcr_lanes<T>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
+        else pcr_lanes<T, LPL>(k & 63, nseg >> wpl_log2, Ra, Rc, Rd);
         XR = Rd * fast_rcp<T>(T(1) + Ra + Rc);
         cur ^= 1;
         if (part) *reinterpret_cast<T*>(xslot(cur, kseg)) = XR;

@@ -78,15 +78,19 @@ __device__ __forceinline__ void pcr_wave64(int j, T& Ra, T& Rc, T& Rd) {
     pcr_row_step<8>(Ra, Rc, Rd);
 }
 
-// nl rows (a power of two, at most 64) in lanes base .. base + nl - 1, row j
-// in lane base + j.  Every lane must call it.  (No early end here: in this
-// rolled loop the tests cost 129^2 FP64 with walls at ncfl 1000, where they
-// never hold, 4.7 %, and gained ragged FP32 lines at ncfl 10 nothing.)
-template <typename T>
+// nl rows (a power of two, at most LPL) in the first lanes of each group of
+// LPL lanes (a line's), row j in lane j of the group; the lanes after them
+// combine rows too, unused.  Every lane must call it.  (No early end here: in
+// this rolled loop the tests cost 129^2 FP64 with walls at ncfl 1000, where they
+// never hold, 4.7 %, and gained ragged FP32 lines at ncfl 10 nothing.  A whole
+// wave per line needs no group base: with one in a register the FP64 sweep of 8
+// cells per lane with walls takes 129 of them, one more than four waves per SIMD
+// leave it.)
+template <typename T, int LPL>
 __device__ __forceinline__ void pcr_lanes(int lane, int nl, T& Ra, T& Rc, T& Rd) {
-    const int base = lane & ~(nl - 1);
+    const int base = LPL == 64 ? 0 : lane & ~(LPL - 1);
     for (int s = 1; s < nl; s <<= 1)
-        pcr_shfl_step<T>(Ra, Rc, Rd, base + ((lane - s) & (nl - 1)), base + ((lane + s) & (nl - 1)));
+        pcr_shfl_step<T>(Ra, Rc, Rd, base | ((lane - s) & (nl - 1)), base | ((lane + s) & (nl - 1)));
 }
 
 }  // namespace asd
