@@ -69,9 +69,9 @@ int asd_batch_set_graphs(asd_batch b, int32_t on);
  * (EUNSUPPORTED if some problem's lines do not fit). */
 int asd_batch_set_block(asd_batch b, int32_t nthreads);
 
-/* Tile body of the batch kernels (ASD_SWEEP_FACE_SLOTS, the default, or
- * ASD_SWEEP_CELL_SLOTS; see asd_set_sweep_kernel) at the current work-group
- * size: EINVAL for another value, EUNSUPPORTED if some problem's lines do
+/* Tile body of the batch kernels (ASD_SWEEP_FACE_SLOTS or
+ * ASD_SWEEP_CELL_SLOTS, the default of FP32 batches without T = 0 walls; see
+ * asd_set_sweep_kernel) at the current work-group size: EINVAL for another value, EUNSUPPORTED if some problem's lines do
  * not fit that body. */
 int asd_batch_set_variant(asd_batch b, int32_t variant);
 int asd_batch_get_variant(asd_batch b, int32_t *variant);

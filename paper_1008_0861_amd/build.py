@@ -31,7 +31,7 @@ SOURCE_FLAGS = {"sweep.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
 
 # Sources whose kernel instantiations are shared out over several objects
 # (each compiled with -DASD_PART=i), so that they compile side by side.
-PARTS = {"batch.hip": 6, "sweep.hip": 8}
+PARTS = {"batch.hip": 12, "sweep.hip": 8}
 
 
 def _compile(unit):

@@ -66,47 +66,47 @@ __device__ __forceinline__ void block_reduce3(double s, M mn, M mx, double& S, d
 
 // One line tile of a batch problem on either tile body (CELL: the
 // cell-slot body of sweep_cell.h).  Both end with a block barrier.
-template <typename T, int MMAX, int LIMC, bool EXT, bool CELL, bool REUSE, int LPL = 64>
+template <typename T, int MMAX, int LIM, bool EXT, bool CELL, bool REUSE, int LPL = 64>
 __device__ __forceinline__ void batch_tile(const SweepParams<T>& P, int l1_0, unsigned char* smem, double& lsum,
                                            T& lmin, T& lmax) {
     if constexpr (CELL)
-        cell::sweep_tile<T, 2, MMAX, LIMC, EXT>(P, l1_0, 0, smem, lsum, lmin, lmax);
+        cell::sweep_tile<T, 2, MMAX, LIM, EXT>(P, l1_0, 0, smem, lsum, lmin, lmax);
     else
-        sweep_tile<T, 2, MMAX, LIMC, EXT, REUSE, LPL>(P, l1_0, 0, smem, lsum, lmin, lmax);
+        sweep_tile<T, 2, MMAX, LIM, EXT, REUSE, LPL>(P, l1_0, 0, smem, lsum, lmin, lmax);
 }
 // The tile at the problem's own capacity mm (MMAX, MMAX / 2, or 4 in the
 // capacity-16 kernels) and line packing (half: two lines per wave,
 // capacity-16 face-body kernels only); uniform over the block, which
 // belongs to one problem.
-template <typename T, int MMAX, int LIMC, bool EXT, bool CELL, bool REUSE>
+template <typename T, int MMAX, int LIM, bool EXT, bool CELL, bool REUSE>
 __device__ __forceinline__ void batch_tile_cap(int mm, int half, const SweepParams<T>& P, int l1_0,
                                                unsigned char* smem, double& lsum, T& lmin, T& lmax) {
     if constexpr (MMAX == 16 && !CELL) {
         if (half) {
-            batch_tile<T, MMAX, LIMC, EXT, CELL, REUSE, 32>(P, l1_0, smem, lsum, lmin, lmax);
+            batch_tile<T, MMAX, LIM, EXT, CELL, REUSE, 32>(P, l1_0, smem, lsum, lmin, lmax);
             return;
         }
     }
     if constexpr (MMAX == 16) {
         if (mm <= 4) {
-            batch_tile<T, 4, LIMC, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
+            batch_tile<T, 4, LIM, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
             return;
         }
     }
     if constexpr (MMAX >= 4) {
         if (mm < MMAX) {
-            batch_tile<T, MMAX / 2, LIMC, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
+            batch_tile<T, MMAX / 2, LIM, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
             return;
         }
     }
-    batch_tile<T, MMAX, LIMC, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
+    batch_tile<T, MMAX, LIM, EXT, CELL, REUSE>(P, l1_0, smem, lsum, lmin, lmax);
 }
 template <typename T, int MMAX, bool CELL>
 struct BatchBounds {
     static constexpr int max_threads = CELL ? SweepCellBounds<T, MMAX>::max_threads : SweepBounds<T, MMAX>::max_threads;
 };
 
-template <typename T, int MMAX, int LIMC, bool EXT, bool CELL>
+template <typename T, int MMAX, int LIM, bool EXT, bool CELL>
 __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     batch_persistent_kernel(const BatchProblem<T>* probs, const int* off, const int* list, int nsteps, BatchOut out) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
                 T amin = T(__builtin_huge_val()), amax = T(-__builtin_huge_val());
                 const int ng = bp->ngroups[d];
                 for (int g = 0; g < ng; ++g) {
-                    batch_tile_cap<T, MMAX, LIMC, EXT, CELL, true>(bp->mmax[d], bp->half[d], P, g * P.lpw, smem_raw,
+                    batch_tile_cap<T, MMAX, LIM, EXT, CELL, true>(bp->mmax[d], bp->half[d], P, g * P.lpw, smem_raw,
                                                                   lsum, lmin, lmax);
                     acc += lsum;
                     amin = lmin < amin ? lmin : amin;
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     }
 }
 
-template <typename T, int MMAX, int LIMC, bool EXT, bool CELL>
+template <typename T, int MMAX, int LIM, bool EXT, bool CELL>
 __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     batch_grouped_kernel(const BatchProblem<T>* probs, const int* group_start, int nprob, int d, double* partials) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     P.red.partials = partials;
     double lsum;
     T lmin, lmax;
-    batch_tile_cap<T, MMAX, LIMC, EXT, CELL, false>(probs[lo].mmax[d], probs[lo].half[d], P,
+    batch_tile_cap<T, MMAX, LIM, EXT, CELL, false>(probs[lo].mmax[d], probs[lo].half[d], P,
                                                     (b - group_start[lo]) * P.lpw, smem_raw, lsum, lmin, lmax);
     // block b's partial sits at index b: problem p's y-sweep tiles are
     // tile0[p] .. tile0[p] + ngroups[1] - 1
@@ -258,84 +258,95 @@ __global__ void __launch_bounds__(256) batch_fold_kernel(const BatchProblem<T>* 
     }
 }
 
-template <typename T, int MMAX, int LIMC, bool EXT>
+// The problems of a batch share one limiter and boundary condition (checked
+// by the host), and each pair has its own instantiation (EXT: T = 0 walls): a
+// limiter read at run time costs several branches per face, and the persistent
+// kernel registers that it has not (60 problems FP64, us per step: persistent
+// MC 2082, straight-line 1727; FP32 grouped MC 68.5 and 60.2, with walls van
+// Leer 83.5 and 77.4).
+template <typename T, int MMAX, int LIM, bool EXT>
 static hipError_t set_batch_attrs_lim(int bytes) {
-    const void* fns[] = {(const void*)batch_persistent_kernel<T, MMAX, LIMC, EXT, false>,
-                         (const void*)batch_grouped_kernel<T, MMAX, LIMC, EXT, false>,
-                         (const void*)batch_persistent_kernel<T, MMAX, LIMC, EXT, true>,
-                         (const void*)batch_grouped_kernel<T, MMAX, LIMC, EXT, true>};
+    const void* fns[] = {(const void*)batch_persistent_kernel<T, MMAX, LIM, EXT, false>,
+                         (const void*)batch_grouped_kernel<T, MMAX, LIM, EXT, false>,
+                         (const void*)batch_persistent_kernel<T, MMAX, LIM, EXT, true>,
+                         (const void*)batch_grouped_kernel<T, MMAX, LIM, EXT, true>};
     for (const void* f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
-template <typename T, int MMAX>
+template <typename T, int MMAX, bool EXT>
 hipError_t set_batch_attrs(int bytes) {
-    hipError_t e = set_batch_attrs_lim<T, MMAX, LIM_VANLEER, false>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, -1, false>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, -1, true>(bytes);
+    hipError_t e = set_batch_attrs_lim<T, MMAX, LIM_VANLEER, EXT>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, LIM_MINMOD, EXT>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, LIM_MC, EXT>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_lim<T, MMAX, LIM_LINEAR, EXT>(bytes);
     return e;
 }
 
-// The problems of a batch share one limiter and boundary condition
-// (checked by the host); van Leer without walls has its own straight-line
-// instantiation, T = 0 walls take the EXT one.
-#define ASD_BATCH_LAUNCH_BODY(KERNEL, MM, CELL, ...)                                        \
-    do {                                                                                    \
-        if (dirichlet)                                                                      \
-            hipLaunchKernelGGL((KERNEL<T, MM, -1, true, CELL>), __VA_ARGS__);               \
-        else if (limiter == LIM_VANLEER)                                                    \
-            hipLaunchKernelGGL((KERNEL<T, MM, LIM_VANLEER, false, CELL>), __VA_ARGS__);     \
-        else                                                                                \
-            hipLaunchKernelGGL((KERNEL<T, MM, -1, false, CELL>), __VA_ARGS__);              \
-    } while (0)
-#define ASD_BATCH_LAUNCH(KERNEL, MM, ...)                                                   \
-    do {                                                                                    \
-        if (variant == SWEEP_CELL_SLOTS) ASD_BATCH_LAUNCH_BODY(KERNEL, MM, true, __VA_ARGS__);  \
-        else ASD_BATCH_LAUNCH_BODY(KERNEL, MM, false, __VA_ARGS__);                         \
-    } while (0)
+#define ASD_BATCH_LAUNCH_LIM(KERNEL, LIM, ...)                                                                    \
+    case LIM:                                                                                                     \
+        if (variant == SWEEP_CELL_SLOTS) hipLaunchKernelGGL((KERNEL<T, MMAX, LIM, EXT, true>), __VA_ARGS__);      \
+        else hipLaunchKernelGGL((KERNEL<T, MMAX, LIM, EXT, false>), __VA_ARGS__);                                 \
+        return hipGetLastError();
+#define ASD_BATCH_LAUNCH(KERNEL, ...)                        \
+    switch (limiter) {                                       \
+        ASD_BATCH_LAUNCH_LIM(KERNEL, LIM_VANLEER, __VA_ARGS__) \
+        ASD_BATCH_LAUNCH_LIM(KERNEL, LIM_MINMOD, __VA_ARGS__)  \
+        ASD_BATCH_LAUNCH_LIM(KERNEL, LIM_MC, __VA_ARGS__)      \
+        ASD_BATCH_LAUNCH_LIM(KERNEL, LIM_LINEAR, __VA_ARGS__)  \
+        default: return hipErrorInvalidValue;                \
+    }
 
-template <typename T, int MMAX>
+template <typename T, int MMAX, bool EXT>
 hipError_t launch_persistent_cap(const BatchProblem<T>* probs, const int* off, const int* list, int nwg, int nsteps,
-                                 int nthreads, size_t lds, int limiter, int dirichlet, int variant, const BatchOut& out,
-                                 hipStream_t st) {
-    ASD_BATCH_LAUNCH(batch_persistent_kernel, MMAX, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out);
-    return hipGetLastError();
+                                 int nthreads, size_t lds, int limiter, int variant, const BatchOut& out, hipStream_t st) {
+    ASD_BATCH_LAUNCH(batch_persistent_kernel, dim3(nwg), dim3(nthreads), lds, st, probs, off, list, nsteps, out)
 }
-template <typename T, int MMAX>
+template <typename T, int MMAX, bool EXT>
 hipError_t launch_grouped_cap(const BatchProblem<T>* probs, const int* group_start, int nprob, int ngroups, int d,
-                              int nthreads, size_t lds, int limiter, int dirichlet, int variant, double* partials,
-                              hipStream_t st) {
-    ASD_BATCH_LAUNCH(batch_grouped_kernel, MMAX, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials);
-    return hipGetLastError();
+                              int nthreads, size_t lds, int limiter, int variant, double* partials, hipStream_t st) {
+    ASD_BATCH_LAUNCH(batch_grouped_kernel, dim3(ngroups), dim3(nthreads), lds, st, probs, group_start, nprob, d, partials)
 }
 #undef ASD_BATCH_LAUNCH
-#undef ASD_BATCH_LAUNCH_BODY
+#undef ASD_BATCH_LAUNCH_LIM
 
-// One object per (type, capacity) compiles its kernels; the first also
+// One object per (type, capacity, EXT) compiles its kernels; the first also
 // holds the entry points that choose between them.
-#define ASD_BATCH_CAP_INST(PRE, T, MM)                                                                              \
-    PRE template hipError_t launch_persistent_cap<T, MM>(const BatchProblem<T>*, const int*, const int*, int, int,  \
-                                                         int, size_t, int, int, int, const BatchOut&, hipStream_t); \
-    PRE template hipError_t launch_grouped_cap<T, MM>(const BatchProblem<T>*, const int*, int, int, int, int,       \
-                                                      size_t, int, int, int, double*, hipStream_t);                 \
-    PRE template hipError_t set_batch_attrs<T, MM>(int);
+#define ASD_BATCH_CAP_INST(PRE, T, MM, EXT)                                                                         \
+    PRE template hipError_t launch_persistent_cap<T, MM, EXT>(const BatchProblem<T>*, const int*, const int*, int,  \
+                                                              int, int, size_t, int, int, const BatchOut&,          \
+                                                              hipStream_t);                                         \
+    PRE template hipError_t launch_grouped_cap<T, MM, EXT>(const BatchProblem<T>*, const int*, int, int, int, int,  \
+                                                           size_t, int, int, double*, hipStream_t);                 \
+    PRE template hipError_t set_batch_attrs<T, MM, EXT>(int);
 #if ASD_PART == 0
-ASD_BATCH_CAP_INST(, float, 4)
-ASD_BATCH_CAP_INST(extern, float, 8)
-ASD_BATCH_CAP_INST(extern, float, 16)
-ASD_BATCH_CAP_INST(extern, double, 4)
-ASD_BATCH_CAP_INST(extern, double, 8)
-ASD_BATCH_CAP_INST(extern, double, 16)
+ASD_BATCH_CAP_INST(, float, 4, false)
+ASD_BATCH_CAP_INST(extern, float, 4, true)
+ASD_BATCH_CAP_INST(extern, float, 8, false)
+ASD_BATCH_CAP_INST(extern, float, 8, true)
+ASD_BATCH_CAP_INST(extern, float, 16, false)
+ASD_BATCH_CAP_INST(extern, float, 16, true)
+ASD_BATCH_CAP_INST(extern, double, 4, false)
+ASD_BATCH_CAP_INST(extern, double, 4, true)
+ASD_BATCH_CAP_INST(extern, double, 8, false)
+ASD_BATCH_CAP_INST(extern, double, 8, true)
+ASD_BATCH_CAP_INST(extern, double, 16, false)
+ASD_BATCH_CAP_INST(extern, double, 16, true)
 
+template <typename T, bool EXT>
+static hipError_t set_batch_attrs_type(int bytes) {
+    hipError_t e = set_batch_attrs<T, 4, EXT>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<T, 8, EXT>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs<T, 16, EXT>(bytes);
+    return e;
+}
 hipError_t batch_set_lds_limits(int bytes) {
-    hipError_t e = set_batch_attrs<float, 4>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<float, 8>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<float, 16>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 4>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 8>(bytes);
-    if (e == hipSuccess) e = set_batch_attrs<double, 16>(bytes);
+    hipError_t e = set_batch_attrs_type<float, false>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_type<float, true>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_type<double, false>(bytes);
+    if (e == hipSuccess) e = set_batch_attrs_type<double, true>(bytes);
     return e;
 }
 
@@ -348,9 +359,15 @@ hipError_t launch_batch_persistent(const BatchProblem<T>* probs, const int* off,
                                                 : sweep_max_threads((int)sizeof(T), mmax)))
         return hipErrorInvalidValue;
     switch (mmax) {
-        case 4: return launch_persistent_cap<T, 4>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
-        case 8: return launch_persistent_cap<T, 8>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
-        case 16: return launch_persistent_cap<T, 16>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, dirichlet, variant, out, st);
+        case 4:
+            return dirichlet ? launch_persistent_cap<T, 4, true>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st)
+                             : launch_persistent_cap<T, 4, false>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st);
+        case 8:
+            return dirichlet ? launch_persistent_cap<T, 8, true>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st)
+                             : launch_persistent_cap<T, 8, false>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st);
+        case 16:
+            return dirichlet ? launch_persistent_cap<T, 16, true>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st)
+                             : launch_persistent_cap<T, 16, false>(probs, off, list, nwg, nsteps, nthreads, lds, limiter, variant, out, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -364,9 +381,15 @@ hipError_t launch_batch_grouped(const BatchProblem<T>* probs, const int* group_s
                                                 : sweep_max_threads((int)sizeof(T), mmax)))
         return hipErrorInvalidValue;
     switch (mmax) {
-        case 4: return launch_grouped_cap<T, 4>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
-        case 8: return launch_grouped_cap<T, 8>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
-        case 16: return launch_grouped_cap<T, 16>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, dirichlet, variant, partials, st);
+        case 4:
+            return dirichlet ? launch_grouped_cap<T, 4, true>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st)
+                             : launch_grouped_cap<T, 4, false>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st);
+        case 8:
+            return dirichlet ? launch_grouped_cap<T, 8, true>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st)
+                             : launch_grouped_cap<T, 8, false>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st);
+        case 16:
+            return dirichlet ? launch_grouped_cap<T, 16, true>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st)
+                             : launch_grouped_cap<T, 16, false>(probs, group_start, nprob, ngroups, d, nthreads, lds, limiter, variant, partials, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -396,15 +419,27 @@ ASD_BATCH_INST(float)
 ASD_BATCH_INST(double)
 #undef ASD_BATCH_INST
 #elif ASD_PART == 1
-ASD_BATCH_CAP_INST(, float, 8)
+ASD_BATCH_CAP_INST(, float, 4, true)
 #elif ASD_PART == 2
-ASD_BATCH_CAP_INST(, float, 16)
+ASD_BATCH_CAP_INST(, float, 8, false)
 #elif ASD_PART == 3
-ASD_BATCH_CAP_INST(, double, 4)
+ASD_BATCH_CAP_INST(, float, 8, true)
 #elif ASD_PART == 4
-ASD_BATCH_CAP_INST(, double, 8)
+ASD_BATCH_CAP_INST(, float, 16, false)
+#elif ASD_PART == 5
+ASD_BATCH_CAP_INST(, float, 16, true)
+#elif ASD_PART == 6
+ASD_BATCH_CAP_INST(, double, 4, false)
+#elif ASD_PART == 7
+ASD_BATCH_CAP_INST(, double, 4, true)
+#elif ASD_PART == 8
+ASD_BATCH_CAP_INST(, double, 8, false)
+#elif ASD_PART == 9
+ASD_BATCH_CAP_INST(, double, 8, true)
+#elif ASD_PART == 10
+ASD_BATCH_CAP_INST(, double, 16, false)
 #else
-ASD_BATCH_CAP_INST(, double, 16)
+ASD_BATCH_CAP_INST(, double, 16, true)
 #endif
 
 }  // namespace asd

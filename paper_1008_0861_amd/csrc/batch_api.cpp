@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <vector>
@@ -234,11 +235,14 @@ extern "C" int asd_batch_init(const asd_desc* descs, int32_t nprob, void* dev_ws
     }
     // measured, us per step of the grouped schedule (lines of 64-512 cells):
     // FP32, cell slots, 512 threads, capacity 8: 60 problems 58.6, 8 problems
-    // 18.3, against 66.9 and 20.8 with face slots at capacity 4; FP64, face
-    // slots, 256 threads, capacity 8: 60 problems 110, 96 problems 182,
-    // against 130 and 204 with 512 threads at capacity 4 (16 problems 36.0
-    // and 35.8)
-    rc = descs[0].dtype == ASD_F32 ? batch_shape(b, 512, SWEEP_CELL_SLOTS, 8) : batch_shape(b, 256, SWEEP_FACE_SLOTS, 8);
+    // 18.3, against 66.9 and 20.8 with face slots at capacity 4; with T = 0
+    // walls face slots at capacity 8: 60 problems 69.8, 8 problems 20.8, 256
+    // problems 326, against 81.2, 21.5 and 402 with cell slots (and, persistent,
+    // 60 problems 947 against 935); FP64, face slots, 256 threads, capacity 8: 60
+    // problems 110, 96 problems 182, against 130 and 204 with 512 threads at
+    // capacity 4 (16 problems 36.0 and 35.8)
+    const bool f32 = descs[0].dtype == ASD_F32, walls = descs[0].bc == ASD_BC_DIRICHLET;
+    rc = batch_shape(b, f32 ? 512 : 256, f32 && !walls ? SWEEP_CELL_SLOTS : SWEEP_FACE_SLOTS, 8);
     if (rc) rc = batch_shape(b, 512, SWEEP_FACE_SLOTS);
     if (rc) rc = batch_shape(b, 256, SWEEP_FACE_SLOTS);
     if (rc) {
@@ -458,8 +462,16 @@ static int run_batch_graph(asd_batch b, int nsteps, int mode, double* energy) {
 
 static constexpr int kBatchGraphMaxSteps = 2048;
 
+// The batch kernels' LDS limits, set by a process's first batch step (a
+// program of single grids does not pay for them), before any capture.
+static std::once_flag g_batch_attr_once;
+static hipError_t g_batch_attr_err = hipSuccess;
+
 template <typename T>
 static int batch_step_t(asd_batch b, int nsteps, int mode, double* energy) {
+    std::call_once(g_batch_attr_once, [] { g_batch_attr_err = batch_set_lds_limits((int)kLdsLimit); });
+    if (g_batch_attr_err != hipSuccess)
+        return asd_fail(ASD_EHIP, "batch kernel attributes: %s", hipGetErrorString(g_batch_attr_err));
     for (int p = 0; p < b->nprob; ++p) {
         asd_grid g = b->sub[p];
         if (!(b->dt[p] > 0.0)) return asd_fail(ASD_ENOTSET, "problem %d has not been set", p);

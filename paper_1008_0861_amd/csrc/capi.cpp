@@ -327,10 +327,7 @@ static int enqueue_coef(asd_grid g, int d, double dt, const void* U) {
 
 template <typename T>
 static int do_prepare(asd_grid g, double dt) {
-    std::call_once(g_attr_once, [] {
-        g_attr_err = sweep_set_lds_limits((int)kLdsLimit);
-        if (g_attr_err == hipSuccess) g_attr_err = batch_set_lds_limits((int)kLdsLimit);
-    });
+    std::call_once(g_attr_once, [] { g_attr_err = sweep_set_lds_limits((int)kLdsLimit); });
     if (g_attr_err != hipSuccess) return hip_check(g_attr_err, "kernel attributes");
     if (!g->ws_inited) {
         int rc = hip_check(launch_fill_u32(g->flags, 0u, 1, g->st), "fill");
