@@ -361,8 +361,11 @@ static int batch_tables(asd_batch b) {
     }
     for (int p = 0; p < np; ++p) probs[p].tile0 = b->h_gs[1][p];
     if (b->ngroups[1] > b->ring_tiles) return asd_fail(ASD_EUNSUPPORTED, "more y-sweep tiles than ring entries");
-    // synchronous uploads: the tables change only with the problem set
-    hipError_t e = hipMemcpy(b->d_probs, b->h_probs.data(), b->h_probs.size(), hipMemcpyHostToDevice);
+    // synchronous uploads (the tables change only with the problem set), after
+    // the batch's stream: an earlier call's kernels may still be reading the
+    // tables, and the copies do not wait for a non-blocking stream
+    hipError_t e = hipStreamSynchronize(b->st);
+    if (e == hipSuccess) e = hipMemcpy(b->d_probs, b->h_probs.data(), b->h_probs.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->d_off, b->h_off.data(), sizeof(int) * b->h_off.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->d_list, b->h_list.data(), sizeof(int) * b->h_list.size(), hipMemcpyHostToDevice);
     for (int d = 0; d < 2 && e == hipSuccess; ++d)
