@@ -130,7 +130,10 @@ int asd_set_sweep_shape(asd_grid g, int32_t axis, int32_t wpl, int32_t lpw, int3
  *   ASD_SWEEP_CELL_SLOTS (1): cells staged as 16-byte slots, faces evaluated
  *       in the solve (a shorter staging chain; io must be 1).
  * EINVAL for a bad argument, EUNSUPPORTED if the shape does not fit the
- * register or LDS budget of that body.  The autotuner (asd_tune) tries both. */
+ * register or LDS budget of that body.  A 4-step grid runs a direction's two
+ * solves in one launch where every axis has face slots with io = 1 and the
+ * larger tile fits (with fewer lines per workgroup than set, where it must; the
+ * getters report that), and in two launches of the bodies set otherwise. */
 #define ASD_SWEEP_FACE_SLOTS 0
 #define ASD_SWEEP_CELL_SLOTS 1
 int asd_set_sweep_kernel(asd_grid g, int32_t axis, int32_t wpl, int32_t lpw, int32_t io, int32_t variant);
@@ -142,10 +145,27 @@ int asd_get_sweep_io(asd_grid g, int32_t axis, int32_t *io);
  * along `axis`. */
 int asd_get_sweep_variant(asd_grid g, int32_t axis, int32_t *variant);
 
-/* Time every admissible (tile body, wpl, lpw, io) of each sweep on the grid's stream with
+/* How the sweep along `axis` stores (2-D grids): in the layout that the next
+ * sweep reads (ASD_STORE_TRANSPOSED), or line-contiguous followed by a
+ * transpose (ASD_STORE_LINES), the default on large grids.  The shape getters
+ * report the shape in use with the current store.  asd_set_sweep_kernel (and
+ * the other shape setters) set the shape of a transposed store;
+ * asd_set_sweep_store(ASD_STORE_LINES) after it makes it the line-contiguous
+ * store's, so that getting shape and store and setting them again in that order
+ * restores both (launches without such a store, the adjoint's, then take the
+ * default shape).  EINVAL for another value, EUNSUPPORTED for ASD_STORE_LINES in
+ * 3-D. */
+#define ASD_STORE_TRANSPOSED 0
+#define ASD_STORE_LINES 1
+int asd_get_sweep_store(asd_grid g, int32_t axis, int32_t *store);
+int asd_set_sweep_store(asd_grid g, int32_t axis, int32_t store);
+
+/* Time the admissible (tile body, wpl, lpw, io) of each sweep on the grid's stream with
  * HIP events (reps whole steps each, best of three timings, T -> workspace,
- * T unchanged) and keep the fastest; two passes over the axes.  Needs T and
- * b set.  Synchronises the stream. */
+ * T unchanged) and keep the fastest; two passes over the axes, and the
+ * line-contiguous store on 2-D grids of 16 MiB and more.  FP32 2-D grids are
+ * tried on one tile body: face slots with T = 0 walls, cell slots below 2^18
+ * cells without.  Needs T and b set.  Synchronises the stream. */
 int asd_tune(asd_grid g, double dt, int32_t reps);
 
 /* hipGraph capture of multi-step calls (only with a non-default stream):

@@ -42,7 +42,7 @@ EXPORTED = [
     "asd_batch_step_energy", "asd_batch_status",
     "asd_batch_set_graphs",
     "asd_get_sweep_config", "asd_set_sweep_config", "asd_set_sweep_shape", "asd_get_sweep_io",
-    "asd_set_sweep_kernel", "asd_get_sweep_variant", "asd_tune",
+    "asd_set_sweep_kernel", "asd_get_sweep_variant", "asd_get_sweep_store", "asd_set_sweep_store", "asd_tune",
     "asd_set_graphs",
     "asd_bench_sweep", "asd_bench_copy", "asd_bench_copy_wide",
     "asd_noalloc_scratch_bytes", "asd_step_semi_implicit_noalloc",
@@ -120,6 +120,8 @@ def lib():
             "asd_get_sweep_io": (ctypes.c_int, [vp, i32, P(i32)]),
             "asd_set_sweep_kernel": (ctypes.c_int, [vp, i32, i32, i32, i32, i32]),
             "asd_get_sweep_variant": (ctypes.c_int, [vp, i32, P(i32)]),
+            "asd_get_sweep_store": (ctypes.c_int, [vp, i32, P(i32)]),
+            "asd_set_sweep_store": (ctypes.c_int, [vp, i32, i32]),
             "asd_tune": (ctypes.c_int, [vp, dbl, i32]),
             "asd_set_graphs": (ctypes.c_int, [vp, i32]),
             "asd_bench_sweep": (ctypes.c_int, [vp, i32, dbl, i32]),
@@ -325,16 +327,23 @@ class Grid:
         return gT, gC
 
     def sweep_config(self, axis):
-        w, l, p, m, io, v = (ctypes.c_int32() for _ in range(6))
+        w, l, p, m, io, v, s = (ctypes.c_int32() for _ in range(7))
         check(lib().asd_get_sweep_config(self.handle, int(axis), ctypes.byref(w), ctypes.byref(l),
                                          ctypes.byref(p), ctypes.byref(m)))
         check(lib().asd_get_sweep_io(self.handle, int(axis), ctypes.byref(io)))
         check(lib().asd_get_sweep_variant(self.handle, int(axis), ctypes.byref(v)))
-        return dict(wpl=w.value, lpw=l.value, P=p.value, mmax=m.value, io=io.value, variant=v.value)
+        check(lib().asd_get_sweep_store(self.handle, int(axis), ctypes.byref(s)))
+        c = dict(wpl=w.value, lpw=l.value, P=p.value, mmax=m.value, io=io.value, variant=v.value)
+        if s.value:
+            c["split"] = True  # line-contiguous store and a transpose
+        return c
 
-    def set_sweep_config(self, axis, wpl, lpw, io=1, variant=0):
-        """variant 0: face-slot tile body, 1: cell-slot tile body."""
+    def set_sweep_config(self, axis, wpl, lpw, io=1, variant=0, split=False):
+        """variant 0: face-slot tile body, 1: cell-slot tile body; split: the
+        line-contiguous store (2-D), which sweep_config reports where it is in use."""
         check(lib().asd_set_sweep_kernel(self.handle, int(axis), int(wpl), int(lpw), int(io), int(variant)))
+        if split:
+            check(lib().asd_set_sweep_store(self.handle, int(axis), 1))
 
     def tune(self, dt, reps=20):
         check(lib().asd_tune(self.handle, float(dt), int(reps)))

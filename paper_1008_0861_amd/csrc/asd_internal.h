@@ -282,10 +282,32 @@ enum : int {
 template <typename T>
 int fill_sweep_params(asd_grid g, int d, const void* in, void* out, int rhs_mode, const SweepCfg& c,
                       asd::SweepParams<T>* P);
-// Whether a 4-step grid runs its two solves per direction in one launch:
-// the coefficients are those of the step (not chi(T), whose second solve has
-// its own) and the larger tile fits on every axis.
-bool four_step_twice(asd_grid g, const SweepCfg* cfg);
+bool set_default_cfg(asd_grid_s* g, int q);
+// Whether axis q stores line-contiguous by default, and the shape it does that
+// in (2-D; filled whether or not).
+bool default_line_cfg(asd_grid_s* g, int q, SweepCfg* out);
+// What one step of a grid launches: per axis the shape and the store, and for
+// the 4-step scheme whether a direction's two solves share a launch (twice) or
+// take one each (two).
+struct StepPlan {
+    SweepCfg cfg[3];
+    bool split[3] = {false, false, false};  // line-contiguous store, then a transpose
+    bool twice = false, two = false;
+};
+// The plan with launch shapes cfg[], or line[] on the axes with split[].  The
+// two solves share a launch when the coefficients are those of the step (not
+// chi(T), whose second solve has its own), every axis has the face body with
+// io = 1 and the larger tile fits on every axis (with fewer lines per workgroup
+// than the shape says, where it must); two launches need both spare states, so
+// that they store transposed.
+StepPlan step_plan(asd_grid g, const SweepCfg* cfg, const SweepCfg* line, const bool* split);
+inline StepPlan step_plan(asd_grid g) { return step_plan(g, g->cfg, g->split_cfg, g->split); }
+// Direction d of a step: in -> out, by way of spare where the plan takes two
+// launches or a transpose (spare is then not in or out; out may be in).
+// mode: SWEEP_SOURCE, SWEEP_REDUCE_INPUT.  coef: chi(T)'s coefficients from
+// each launch's input first.
+int enqueue_direction(asd_grid g, const StepPlan& plan, int d, double dt, const void* in, void* spare, void* out,
+                      int mode, const asd::ReduceParams& red, int* nblocks_out, bool coef);
 int check_fields(asd_grid g, bool need_T);
 int prepare(asd_grid g, double dt);  // dt > 0: face coefficients for dt
 int64_t layout_stride(const asd_grid g, int L, int a);

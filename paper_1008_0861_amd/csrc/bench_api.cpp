@@ -14,7 +14,7 @@ extern "C" int asd_get_sweep_config(asd_grid g, int32_t axis, int32_t* wpl, int3
     if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
     if (axis < 0 || axis >= g->d.ndim) return asd_fail(ASD_EINVAL, "bad axis %d", axis);
     if (!wpl || !lpw || !P || !mmax) return asd_fail(ASD_EINVAL, "NULL output");
-    const SweepCfg& c = g->cfg[axis];
+    const SweepCfg c = step_plan(g).cfg[axis];
     *wpl = c.wpl;
     *lpw = c.lpw;
     *P = c.P;
@@ -57,7 +57,7 @@ extern "C" int asd_get_sweep_io(asd_grid g, int32_t axis, int32_t* io) {
     if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
     if (axis < 0 || axis >= g->d.ndim) return asd_fail(ASD_EINVAL, "bad axis %d", axis);
     if (!io) return asd_fail(ASD_EINVAL, "NULL output");
-    *io = g->cfg[axis].io;
+    *io = step_plan(g).cfg[axis].io;
     return ASD_OK;
 }
 
@@ -65,7 +65,34 @@ extern "C" int asd_get_sweep_variant(asd_grid g, int32_t axis, int32_t* variant)
     if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
     if (axis < 0 || axis >= g->d.ndim) return asd_fail(ASD_EINVAL, "bad axis %d", axis);
     if (!variant) return asd_fail(ASD_EINVAL, "NULL output");
-    *variant = g->cfg[axis].variant;
+    *variant = step_plan(g).cfg[axis].variant;
+    return ASD_OK;
+}
+
+extern "C" int asd_get_sweep_store(asd_grid g, int32_t axis, int32_t* store) {
+    if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
+    if (axis < 0 || axis >= g->d.ndim) return asd_fail(ASD_EINVAL, "bad axis %d", axis);
+    if (!store) return asd_fail(ASD_EINVAL, "NULL output");
+    *store = step_plan(g).split[axis] ? ASD_STORE_LINES : ASD_STORE_TRANSPOSED;
+    return ASD_OK;
+}
+
+extern "C" int asd_set_sweep_store(asd_grid g, int32_t axis, int32_t store) {
+    if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
+    if (axis < 0 || axis >= g->d.ndim) return asd_fail(ASD_EINVAL, "bad axis %d", axis);
+    if (store != ASD_STORE_TRANSPOSED && store != ASD_STORE_LINES)
+        return asd_fail(ASD_EINVAL, "store must be ASD_STORE_TRANSPOSED or _LINES");
+    if (store == ASD_STORE_LINES && g->d.ndim != 2)
+        return asd_fail(ASD_EUNSUPPORTED, "the line-contiguous store is for 2-D grids");
+    if ((store == ASD_STORE_LINES) == g->split[axis]) return ASD_OK;
+    if (store == ASD_STORE_LINES) {
+        g->split_cfg[axis] = g->cfg[axis];
+        (void)set_default_cfg(g, axis);
+    } else {
+        g->cfg[axis] = g->split_cfg[axis];
+    }
+    g->split[axis] = store == ASD_STORE_LINES;
+    g->graph_valid = false;
     return ASD_OK;
 }
 
@@ -78,20 +105,16 @@ extern "C" int asd_set_graphs(asd_grid g, int32_t mode) {
     return ASD_OK;
 }
 
-// Buffers of sweep `axis` run in isolation: input = the state that sweep
-// reads during a step (T for the first sweep, else a scratch state), output
-// = a scratch state that no later timed launch reads.  T is never written.
-static void bench_buffers(asd_grid g, int axis, const void** in, void** out) {
-    if (axis == 0) {
-        *in = g->T;
-        *out = g->tmp[0];
-    } else if (axis == 1) {
-        *in = g->tmp[0];
-        *out = g->tmp[1];
-    } else {
-        *in = g->tmp[1];
-        *out = g->tmp[0];
-    }
+// Direction `axis` run in isolation, as the step loop runs it: from T (the
+// first) or the scratch state that the direction before it wrote, to a scratch
+// state.  T is never written: a direction that goes by way of a third state (two
+// launches, or a transpose) and starts from a scratch state ends in that one.
+static int bench_direction(asd_grid g, const StepPlan& plan, int axis, double dt) {
+    const bool via = plan.two || plan.split[axis];
+    void* const own = axis == 1 ? g->tmp[0] : g->tmp[1];    // the input, but for axis 0
+    void* const other = axis == 1 ? g->tmp[1] : g->tmp[0];
+    if (axis == 0) return enqueue_direction(g, plan, 0, dt, g->T, own, other, 0, no_reduce(), nullptr, false);
+    return enqueue_direction(g, plan, axis, dt, own, other, via ? own : other, 0, no_reduce(), nullptr, false);
 }
 
 // Fill the scratch inputs of sweeps 1.. with one real sweep chain from T.
@@ -114,11 +137,9 @@ extern "C" int asd_bench_sweep(asd_grid g, int32_t axis, double dt, int32_t reps
     rc = prepare(g, dt);
     if (rc) return rc;
     if (reps == 0) return bench_prepare_inputs(g, dt);
-    const void* in;
-    void* out;
-    bench_buffers(g, axis, &in, &out);
+    const StepPlan plan = step_plan(g);
     for (int r = 0; r < reps; ++r) {
-        rc = enqueue_sweep(g, axis, dt, in, out, 0, no_reduce(), nullptr, nullptr);
+        rc = bench_direction(g, plan, axis, dt);
         if (rc) return rc;
     }
     return ASD_OK;
@@ -143,11 +164,10 @@ extern "C" int asd_bench_copy_wide(const void* src, void* dst, size_t nbytes, vo
 
 // ------------------------------------------------------------- autotuner
 
-// Time reps whole steps (every sweep in order, each reading what the
-// previous one wrote, as in the step loop) with the launch shapes cfg[]
-// (axes with split[]: line-contiguous store and a transpose), on the two
-// scratch buffers: the first sweep reads T, T is never written.
-static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, const bool* split, float* ms) {
+// Time reps whole steps of the plan (every direction in order, as the step loop
+// runs it, each reading what the one before wrote) on the two scratch buffers:
+// the first direction reads T, T is never written.
+static int time_chain(asd_grid g, double dt, int reps, const StepPlan& plan, float* ms) {
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return asd_fail(ASD_EHIP, "event create");
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -156,22 +176,16 @@ static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, cons
     }
     const void* in = g->T;
     int cur = 0;  // scratch buffer written next
-    const int mode = four_step_twice(g, cfg) ? SWEEP_TWICE : 0;
     auto chain = [&](int steps) {
         int rc = ASD_OK;
         for (int s = 0; s < steps && !rc; ++s)
             for (int d = 0; d < g->d.ndim && !rc; ++d) {
-                void* out = g->tmp[cur];
-                rc = enqueue_sweep(g, d, dt, in, out, split[d] ? mode | SWEEP_KEEP_LAYOUT : mode, no_reduce(), &cfg[d],
-                                   nullptr);
-                if (split[d] && !rc) {
-                    // back over the sweep's input, which it has read by then
-                    void* to = g->tmp[cur ^ 1];
-                    rc = enqueue_permute_2d(g, out, to, d == 0);
-                    out = to;
-                } else {
-                    cur ^= 1;
-                }
+                // by way of one scratch buffer: back over the direction's
+                // input, which the launches have read by then
+                const bool via = plan.two || plan.split[d];
+                void* out = g->tmp[via ? cur ^ 1 : cur];
+                rc = enqueue_direction(g, plan, d, dt, in, g->tmp[cur], out, 0, no_reduce(), nullptr, false);
+                if (!via) cur ^= 1;
                 in = out;
             }
         return rc;
@@ -190,11 +204,14 @@ static int time_chain(asd_grid g, double dt, int reps, const SweepCfg* cfg, cons
 // Autotuner: for each sweep axis in turn, every admissible (tile body,
 // waves per line, lines per workgroup, io) shape is timed inside whole steps
 // (the other axes at their current shapes), and the fastest is kept; two
-// passes.  On 2-D grids of 16 MiB and more the line-contiguous store with a
-// transpose is tried too, in its default shape (on smaller grids the extra
-// passes cost more than short pieces of a transposed store, which meet in the
-// L2).  A shape's time is the best of three timings: shapes a few per cent
-// apart are otherwise ranked by the noise of a single sub-millisecond timing.
+// passes.  Every trial is timed as the step loop would run it: on a 4-step grid
+// a shape whose two solves do not fit one launch, or not on that body, takes two
+// launches on every axis, and no transpose.  On 2-D grids of 16 MiB and more the
+// line-contiguous store with a transpose is tried too, in its default shape (on
+// smaller grids the extra passes cost more than short pieces of a transposed
+// store, which meet in the L2).  A shape's time is the best of three timings:
+// shapes a few per cent apart are otherwise ranked by the noise of a single
+// sub-millisecond timing.
 extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
     if (!g) return asd_fail(ASD_EINVAL, "grid is NULL");
     if (!(std::isfinite(dt) && dt > 0.0)) return asd_fail(ASD_EINVAL, "dt must be finite and > 0");
@@ -214,21 +231,23 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
     const int last_body = f32_2d && walls ? SWEEP_FACE_SLOTS : SWEEP_CELL_SLOTS;
     const int first_body = f32_2d && !walls && g->N < (1 << 18) ? SWEEP_CELL_SLOTS : SWEEP_FACE_SLOTS;
     const bool try_split = g->d.ndim == 2 && g->N * (int64_t)g->es >= ((int64_t)16 << 20);
-    auto best_of_three = [&](const SweepCfg* trial, const bool* sp, float* ms) {
+    auto best_of_three = [&](const StepPlan& plan, float* ms) {
         *ms = 1e30f;
         int r = ASD_OK;
         for (int t = 0; t < 3 && !r; ++t) {
             float one = 0.f;
-            r = time_chain(g, dt, reps, trial, sp, &one);
+            r = time_chain(g, dt, reps, plan, &one);
             *ms = std::min(*ms, one);
         }
         return r;
     };
     SweepCfg line[3];  // the line-contiguous shapes
+    for (int a = 0; a < g->d.ndim; ++a) (void)default_line_cfg(g, a, &line[a]);
     for (int pass = 0; pass < 2; ++pass) {
         for (int axis = 0; axis < g->d.ndim; ++axis) {
             SweepCfg best = cur[axis];
             float best_ms = 1e30f;
+            split[axis] = false;
             for (int variant = first_body; variant <= last_body; ++variant)
             for (int io = 1; io <= (variant == SWEEP_CELL_SLOTS ? 1 : 2); ++io)
             for (int wpl = 1; wpl <= 16; wpl *= 2) {
@@ -237,12 +256,13 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
                     if (!choose_sweep_cfg((int)g->es, g->d.ndim, (int)g->d.n[axis], chi, wpl, lpw, &c, io, variant))
                         continue;
                     if (c.wpl != wpl || c.lpw != lpw || c.io != io || c.variant != variant) continue;
-                    SweepCfg trial[3] = {split[0] ? line[0] : cur[0], split[1] ? line[1] : cur[1], cur[2]};
+                    SweepCfg trial[3] = {cur[0], cur[1], cur[2]};
                     trial[axis] = c;
-                    bool sp[3] = {split[0], split[1], false};
-                    sp[axis] = false;
+                    const StepPlan plan = step_plan(g, trial, line, split);
+                    // (the two-solve launch of a shape with fewer lines per workgroup)
+                    if (plan.cfg[axis].lpw != lpw) continue;
                     float ms = 1e30f;
-                    rc = best_of_three(trial, sp, &ms);
+                    rc = best_of_three(plan, &ms);
                     if (rc) return rc;
                     if (ms < best_ms) {
                         best_ms = ms;
@@ -251,16 +271,11 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
                 }
             }
             cur[axis] = best;
-            split[axis] = false;
             if (try_split) {
-                (void)default_split((int)g->es, 2, (int)g->d.n[axis], (int)g->d.n[1 - axis],
-                                    g->d.bc == ASD_BC_DIRICHLET, &line[axis]);
-                SweepCfg trial[3] = {split[0] ? line[0] : cur[0], split[1] ? line[1] : cur[1], cur[2]};
-                trial[axis] = line[axis];
-                bool sp[3] = {split[0], split[1], false};
-                sp[axis] = true;
+                split[axis] = true;
+                const StepPlan plan = step_plan(g, cur, line, split);
                 float ms = 1e30f;
-                rc = best_of_three(trial, sp, &ms);
+                if (plan.split[axis]) rc = best_of_three(plan, &ms);
                 if (rc) return rc;
                 split[axis] = ms < best_ms;
             }

@@ -158,6 +158,33 @@ extern "C" int asd_workspace_bytes(const asd_desc* desc, size_t* bytes) {
 
 size_t grid_workspace_bytes(const asd_desc* desc) { return plan_ws(desc).total; }
 
+// The default shape of axis q; on a 4-step grid whose two solves fit one
+// launch on every axis, in that launch's form (step_plan then takes it).
+bool set_default_cfg(asd_grid_s* g, int q) {
+    const asd_desc& d = g->d;
+    const int es = (int)g->es;
+    const bool chi = (d.flags & ASD_FLAG_PER_CELL_CHI) != 0, four = (d.flags & ASD_FLAG_FOUR_STEP) != 0;
+    auto shape = [&](int a, SweepCfg* c) {
+        return default_sweep_cfg(es, d.ndim, (int)d.n[a], g->N / d.n[a], chi, four, d.bc == ASD_BC_DIRICHLET, c);
+    };
+    bool twice = four && d.chi_exp == 0.0;
+    SweepCfg c;
+    for (int a = 0; a < d.ndim && twice; ++a)
+        twice = shape(a, &c) && twice_cfg(es, d.ndim, (int)d.n[a], c, &c);
+    if (!shape(q, &g->cfg[q])) return false;
+    if (twice) (void)twice_cfg(es, d.ndim, (int)d.n[q], g->cfg[q], &g->cfg[q]);
+    return true;
+}
+
+bool default_line_cfg(asd_grid_s* g, int q, SweepCfg* out) {
+    const asd_desc& d = g->d;
+    if (d.ndim != 2) return false;
+    const int es = (int)g->es;
+    const bool split = default_split(es, 2, (int)d.n[q], (int)d.n[1 - q], d.bc == ASD_BC_DIRICHLET, out);
+    if (d.flags & ASD_FLAG_FOUR_STEP) (void)twice_cfg(es, 2, (int)d.n[q], *out, out);
+    return split;
+}
+
 int init_grid_in_place(asd_grid_s* g, const asd_desc* desc, void* dev_ws, size_t ws_bytes, void* stream) {
     WsPlan p = plan_ws(desc);
     if (!dev_ws) return asd_fail(ASD_EWORKSPACE, "workspace is NULL");
@@ -180,12 +207,8 @@ int init_grid_in_place(asd_grid_s* g, const asd_desc* desc, void* dev_ws, size_t
     g->flags = (unsigned*)sm;
     g->stats = (double*)(sm + 8);   // 3 doubles
     for (int q = 0; q < desc->ndim; ++q) {
-        if (!default_sweep_cfg((int)g->es, desc->ndim, (int)desc->n[q], g->N / desc->n[q],
-                               (desc->flags & ASD_FLAG_PER_CELL_CHI) != 0, (desc->flags & ASD_FLAG_FOUR_STEP) != 0,
-                               desc->bc == ASD_BC_DIRICHLET, &g->cfg[q]))
-            return asd_fail(ASD_EUNSUPPORTED, "no sweep configuration for axis %d", q);
-        g->split[q] = desc->ndim == 2 && default_split((int)g->es, 2, (int)desc->n[q], (int)desc->n[1 - q],
-                                                       desc->bc == ASD_BC_DIRICHLET, &g->split_cfg[q]);
+        if (!set_default_cfg(g, q)) return asd_fail(ASD_EUNSUPPORTED, "no sweep configuration for axis %d", q);
+        g->split[q] = default_line_cfg(g, q, &g->split_cfg[q]);
     }
     return ASD_OK;
 }
@@ -515,43 +538,66 @@ int check_dt(asd_grid g, double dt, bool explicit_scheme) {
 // slot, and one fold launch turns a full ring (or the last steps) into the
 // outputs of each of those steps, off the sweeps' critical path.
 // Workgroups of one launch of sweep d in launch shape c.
-static int64_t sweep_num_blocks(asd_grid g, int d, SweepCfg c, bool twice) {
+static int64_t sweep_num_blocks(asd_grid g, int d, const SweepCfg& c) {
     const SweepGeom G = sweep_geom(g->d.ndim, d);
     const int64_t nz = g->d.ndim == 3 ? g->d.n[2] : 1;
     const int64_t nax[3] = {g->d.n[0], g->d.n[1], nz};
-    if (twice) (void)twice_cfg((int)g->es, g->d.ndim, (int)g->d.n[d], c, &c);
-    const int lpw = c.lpw;
-    return (nax[G.t1] + lpw - 1) / lpw * nax[G.t2];
+    return (nax[G.t1] + c.lpw - 1) / c.lpw * nax[G.t2];
 }
 
-bool four_step_twice(asd_grid g, const SweepCfg* cfg) {
-    if (!(g->d.flags & ASD_FLAG_FOUR_STEP) || g->d.chi_exp != 0.0) return false;
-    SweepCfg c;
-    for (int d = 0; d < g->d.ndim; ++d)
-        if (!twice_cfg((int)g->es, g->d.ndim, (int)g->d.n[d], cfg[d], &c)) return false;
-    return true;
+StepPlan step_plan(asd_grid g, const SweepCfg* cfg, const SweepCfg* line, const bool* split) {
+    StepPlan p;
+    const int nd = g->d.ndim;
+    for (int d = 0; d < nd; ++d) {
+        p.split[d] = split[d];
+        p.cfg[d] = split[d] ? line[d] : cfg[d];
+    }
+    if (!(g->d.flags & ASD_FLAG_FOUR_STEP)) return p;
+    SweepCfg t[3];
+    p.twice = g->d.chi_exp == 0.0;
+    for (int d = 0; d < nd && p.twice; ++d)
+        p.twice = p.cfg[d].variant == SWEEP_FACE_SLOTS && p.cfg[d].io == 1 &&
+                  twice_cfg((int)g->es, nd, (int)g->d.n[d], p.cfg[d], &t[d]);
+    p.two = !p.twice;
+    for (int d = 0; d < nd; ++d) {
+        p.split[d] = p.split[d] && p.twice;
+        p.cfg[d] = p.twice ? t[d] : cfg[d];
+    }
+    return p;
+}
+
+int enqueue_direction(asd_grid g, const StepPlan& plan, int d, double dt, const void* in, void* spare, void* out,
+                      int mode, const ReduceParams& red, int* nblocks_out, bool coef) {
+    coef = coef && g->d.chi_exp != 0.0;
+    auto launch = [&](const void* a, void* b, int m, const ReduceParams& r, int* nb) {
+        const int rc = coef ? enqueue_coef(g, d, dt, a) : ASD_OK;
+        return rc ? rc : enqueue_sweep(g, d, dt, a, b, m, r, &plan.cfg[d], nb);
+    };
+    if (plan.two) {
+        // transverse term at dt with the first half-step solve, written in the
+        // input layout, then the second half-step solve
+        const int rc = launch(in, spare, mode | SWEEP_KEEP_LAYOUT, no_reduce(), nullptr);
+        return rc ? rc : launch(spare, out, SWEEP_SOLVE_ONLY, red, nblocks_out);
+    }
+    if (plan.twice) mode |= SWEEP_TWICE;
+    if (!plan.split[d]) return launch(in, out, mode, red, nblocks_out);
+    const int rc = launch(in, spare, mode | SWEEP_KEEP_LAYOUT, red, nblocks_out);
+    return rc ? rc : enqueue_permute_2d(g, spare, out, d == 0);
 }
 
 int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     const int nd = g->d.ndim;
-    // 4-step: each direction's two solves in one launch where the tile fits
-    // (256^3 FP32: one pass over memory instead of two), else in two
-    const bool twice = four_step_twice(g, g->cfg);
-    const bool four = (g->d.flags & ASD_FLAG_FOUR_STEP) != 0 && !twice;
-    const int tw = twice ? SWEEP_TWICE : 0;
-    // (two launches per direction of the 4-step scheme need both states)
-    auto split = [&](int d) { return g->split[d] && !four; };
+    const StepPlan plan = step_plan(g);
     const bool reverse = (g->d.flags & ASD_FLAG_REVERSE_ORDER) != 0;  // 2-D only
     int rc = ASD_OK;
     // The initial state's energy: reduced by the first sweep, which reads
     // every cell of it once (one launch per direction in the order x, y, no source), and
     // folded before the first steps' fold; else by a standalone reduction.
-    const bool fuse_e0 = outs.any() && nsteps > 0 && !four && !reverse && !g->src;
+    const bool fuse_e0 = outs.any() && nsteps > 0 && !plan.two && !reverse && !g->src;
     // when the first sweep and the step's last sweep launch as many blocks,
     // the initial state's partials take ring slot 0 and are folded with the
     // first steps' (one fold launch fewer per call)
-    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0, split(0) ? g->split_cfg[0] : g->cfg[0], twice) ==
-                                           sweep_num_blocks(g, nd - 1, split(nd - 1) ? g->split_cfg[nd - 1] : g->cfg[nd - 1], twice);
+    const bool e0_in_ring = fuse_e0 && sweep_num_blocks(g, 0, plan.cfg[0]) == sweep_num_blocks(g, nd - 1, plan.cfg[nd - 1]);
     FoldParams f0{};
     bool f0_pending = false;
     if (outs.any() && !fuse_e0) {
@@ -561,20 +607,9 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     // Reverse order (y, x): the state lives in layout B between steps, in
     // tmp1: T -> tmp1 before the first step, tmp1 -> T after the last.
     if (reverse && nsteps > 0 && rc == ASD_OK) rc = enqueue_permute_2d(g, g->T, g->tmp[1], true);
-    // chi(T) (section 3.3): each sweep's coefficients from that sweep's input
-    const bool chi_of_T = g->d.chi_exp != 0.0;
-    auto sweep = [&](int d, const void* src, void* dst, int mode, const ReduceParams& red, int* nb) {
-        int r = chi_of_T ? enqueue_coef(g, d, dt, src) : ASD_OK;
-        if (r == ASD_OK && split(d)) {
-            // line-contiguous into the spare state, then transposed
-            void* spare = reverse ? g->T : g->tmp[1];
-            r = enqueue_sweep(g, d, dt, src, spare, mode | SWEEP_KEEP_LAYOUT, red, &g->split_cfg[d], nb);
-            if (r == ASD_OK) r = enqueue_permute_2d(g, spare, dst, d == 0);
-        } else if (r == ASD_OK) {
-            r = enqueue_sweep(g, d, dt, src, dst, mode, red, nullptr, nb);
-        }
-        return r;
-    };
+    // two launches per direction and transposes go by way of a state that is
+    // free between them: T in reverse order, else the second scratch
+    void* const spare = reverse ? g->T : g->tmp[1];
     int used = e0_in_ring ? 1 : 0;  // ring slots holding unfolded entries
     for (int s = 0; s < nsteps && rc == ASD_OK; ++s) {
         const void* in = reverse ? g->tmp[1] : g->T;
@@ -587,32 +622,15 @@ int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
             const bool red_in = fuse_e0 && s == 0 && i == 0;
             if (red_in) red.partials = e0_in_ring ? ring_slot(g, 0) : ring_slot(g, g->ring_slots);
             int nb = 0;
-            void* out;
-            if (reverse) {
-                // y: B (tmp1) -> A (tmp0); x: A (tmp0) -> B (tmp1).  The 4-step
-                // intermediate (input layout) goes to T, free meanwhile.
-                out = d == 1 ? g->tmp[0] : g->tmp[1];
-                if (!four) {
-                    rc = sweep(d, in, out, src | tw, red, &nb);
-                } else {
-                    rc = sweep(d, in, g->T, SWEEP_KEEP_LAYOUT | src, no_reduce(), nullptr);
-                    if (rc == ASD_OK) rc = sweep(d, g->T, out, SWEEP_SOLVE_ONLY, red, &nb);
-                }
-            } else if (!four) {
-                out = (d == nd - 1) ? g->T : g->tmp[d];
-                rc = sweep(d, in, out, src | tw | (red_in ? SWEEP_REDUCE_INPUT : 0), red, &nb);
-                if (red_in && !e0_in_ring) {
-                    f0 = make_fold(g, red.partials, nb, 1, outs, 0);
-                    f0_pending = true;
-                }
-            } else {
-                // 4-step: transverse term at dt with the first half-step
-                // solve, written in the input layout, then the second
-                // half-step solve into the next sweep's layout.  States:
-                // T -> tmp0 (-> T in 3-D) -> T.
-                out = d == 0 ? g->tmp[0] : g->T;
-                rc = sweep(d, in, g->tmp[1], SWEEP_KEEP_LAYOUT | src, no_reduce(), nullptr);
-                if (rc == ASD_OK) rc = sweep(d, g->tmp[1], out, SWEEP_SOLVE_ONLY, red, &nb);
+            // reverse order: y: B (tmp1) -> A (tmp0); x: A (tmp0) -> B (tmp1).
+            // Two launches per direction, in 3-D: T -> tmp0 -> T -> T.
+            void* out = reverse ? (d == 1 ? g->tmp[0] : g->tmp[1])
+                        : d == nd - 1 || (plan.two && d > 0) ? g->T
+                                                             : g->tmp[d];
+            rc = enqueue_direction(g, plan, d, dt, in, spare, out, src | (red_in ? SWEEP_REDUCE_INPUT : 0), red, &nb, true);
+            if (red_in && !e0_in_ring) {
+                f0 = make_fold(g, red.partials, nb, 1, outs, 0);
+                f0_pending = true;
             }
             if (rc == ASD_OK && produce && (++used == g->ring_slots || s == nsteps - 1)) {
                 // entry 0 first: the later folds check the drift against it
