@@ -122,54 +122,98 @@ inline bool twice_cfg(int es, int ndim, int n, SweepCfg c, SweepCfg* out) {
     return true;
 }
 
+// Lines that the workgroups on one CU hold at a time in shape c, by their LDS
+// (160 KiB per CU in units of 1280 bytes; the reduction's static share added).
+inline int resident_lines(int es, int ndim, int n, const SweepCfg& c) {
+    const size_t unit = 1280, tile = (sweep_lds(es, ndim, n, c) + 384 + unit - 1) / unit * unit;
+    return (int)(160 * 1024 / tile) * c.lpw;
+}
+
 // Default launch shape of a sweep of `lines` lines of n cells.  Each choice
-// is the measured best over sizes (us per step, all sweeps alike):
+// is the measured best over sizes (us per step, all sweeps alike).  units(l) is
+// the number of lines of the busiest of the 256 CUs with l lines per workgroup.
 // - Lines per workgroup: pieces of at most 16 bytes in the transposed store
 //   (longer ones leave CUs idle or one workgroup per CU: FP32 1024^2 16.6 with
-//   4 lines, 18.9 with 8), fewer where that keeps more CUs busy.  units(l) is
-//   the number of lines of the busiest of the 256 CUs; l grows while it costs
-//   at most a third more: FP32 256^2 7.0 with 1 line, 7.4 with 4; 1200^2 26.6
-//   with 2, over 30 with 4; 4096^2 193 with 4, 436 with 1.
-// - Tile body: cell slots while a tile leaves room for two workgroups per CU
-//   (FP32 1024^2 16.6 against 19.1 with face slots, 2048^2 46 against 38;
-//   FP64 1024^2 22.0 against 27.0, 2048^2 83 against 75).
-// - Waves per line: at most 8 cells per lane with cell slots, 16 with face
-//   slots; FP64 lines of more than 1024 cells take two waves with two lines
-//   per workgroup (1403 x 937 40.5, 50.4 with four waves and one line) unless
-//   that loads a CU more (1200^2 49.2, 43.6) or the line is 2048 or longer
-//   (2048^2 78.9, 75.3).
+//   4 lines, 18.9 with 8), fewer where that keeps more CUs busy: l grows while
+//   it costs at most a third more (FP32 256^2 7.0 with 1 line, 7.4 with 4), on
+//   FP32 lines of more than 1024 cells less than that for the fourth (1536^2
+//   39.0 with 2 lines, 41.0 with 4; 1792^2 41.4, 38.4).
+// - Rows that start on half lines of the cache (64 bytes) keep short pieces
+//   together: at most 2 lines (FP32 2000^2 49.1, 53.3 with 4; 1904^2 46.1, 48.2).
+//   Rows that start anywhere need whole pieces, up to two thirds more load:
+//   FP32 1403^2 35.8 with 4 lines, 47.9 with 2; 1210^2 33.3, 38.1.
+// - FP32 body, above 1024 cells: cell slots while a CU holds six lines of them, or
+//   all that it gets (1392^2 28.4 with 2 lines, face slots 33.7; 1536^2, four
+//   lines, 49.6 and 39.1; 1344^2 with 4 lines per workgroup, four lines, 38.5 and
+//   33.8), on up to 1024 always (1024^2 16.6 against 19.1).
+// - Waves per line: at most 8 cells per lane with cell slots up to 1024 cells, 16
+//   above and with face slots.
+// - FP64, up to 1024 cells: cell slots, on two waves from 7 of a lane's 8 cells up
+//   (1024^2 22.0, face slots 27.0; 960^2 26.3, 29.5; 768^2 30.0, 24.6) or with at
+//   most a line per CU (600 x 60 11.4, 11.8).
+// - FP64, 1025 to 2048: four waves and one line (1400^2 50.6, two waves and two
+//   lines 66.1), but two and two where rows start off the half lines (1403^2
+//   67.8, 83.2; 1100^2 52.1, 62.1) or every lane is nearly full and no CU loaded
+//   more (1920^2 78.0, 81.5).  Longer lines: four waves (3000 x 300 40.5, eight
+//   waves 47.3), eight where there is at most a line per CU (3000 x 100 25.0, 23.9), but for
+//   the two-solve launches (256 x 4096 33.8, eight waves 40.5).
 // - 3-D: FP32 cell slots and 4 lines (256^3 261, face slots 299; 200^3 142,
-//   162), the two-solve launches of the 4-step scheme 8 (293, 299); FP64 face
+//   162), but face slots for lines of 65 to 127 cells, which leave part of a
+//   lane's two cells empty (100^3 34.8, cell slots 36.4; 110^3 35.7, 37.8), and
+//   8 lines for the two-solve launches of the 4-step scheme (293, 299); FP64 face
 //   slots (200^3 290, 312).
-// - FP32 grids of fewer than 2^18 cells, and with T = 0 walls, keep face
-//   slots and one wave per line, with two staging and storing: the two bodies
-//   and other segment lengths round differently, which on so few cells shows
-//   in the FP64 energy (234^2 with walls, 100 steps: 1e-8).  256^2 7.9 (cell
-//   slots 7.0, one staging wave 8.5, four lines per workgroup 9.1).
-inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, bool four, bool walls, SweepCfg* out) {
+// - The two-solve launches (twice) of lines of 1025 to 2048 cells take four waves,
+//   whose second solve finds its registers: FP64 one line (1536^2 106, two waves
+//   and two lines 129; 1403^2 100, 116), FP32 two (1536^2 63.7, 77.8 with two waves
+//   and four lines; 1200^2 45.6, 52.9 with two and two), but for rows off the half
+//   lines above 1420 cells (1500^2 68.8, 66.6; 1700^2 79.4, 70.4) or where that
+//   spares no CU a line (937 x 1403 37.3, 35.3).
+// - FP32 grids of fewer than 2^18 cells, and with T = 0 walls, keep face slots
+//   and one wave per line, with two staging and storing (256^2 7.9; cell slots 7.0,
+//   one staging wave 8.5, four lines per workgroup 9.1): the two bodies round
+//   differently, and a default keeps its results (the energies of both are as
+//   far from 64-bit arithmetic).
+inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, bool twice, bool walls, SweepCfg* out) {
     const bool keep = es == 4 && ndim == 2 && (walls || (int64_t)n * lines < (1 << 18));
     auto units = [&](int64_t l) { return (lines + 256 * l - 1) / (256 * l) * l; };
     int lpw = 1, wpl = 0, io = 1, body = asd::SWEEP_FACE_SLOTS;
     for (int l = 2; l <= 16 / es; l *= 2)
         if (3 * units(l) <= 4 * units(1)) lpw = l;
+    const int64_t row = lines * es % 128;  // of the transposed output
+    const bool aligned = row % 64 == 0;
     if (ndim == 3) {
         if (es == 4 && n <= 512) {
             wpl = 1;
-            if (four) lpw *= 2;
-            else body = asd::SWEEP_CELL_SLOTS;
+            if (twice) lpw *= 2;
+            else if (n <= 64 || n >= 128) body = asd::SWEEP_CELL_SLOTS;
         }
     } else if (keep && n <= 1024) {
         wpl = 1;
         io = n >= 128 ? 2 : 1;
         lpw = std::max(lpw, io);
-    } else if (n <= (es == 8 ? 1024 : 1420)) {
+    } else if (n <= 1024) {
         wpl = n <= 512 ? 1 : 2;
-        body = asd::SWEEP_CELL_SLOTS;
+        if (es == 4 || n <= 512 || n >= 7 * 128 || lines <= 256) body = asd::SWEEP_CELL_SLOTS;
     } else if (es == 8) {
-        wpl = n < 2048 && units(2) == units(1) ? 2 : 4;
+        const bool two = aligned ? n > 14 * 128 && units(2) == units(1) : lpw == 2;
+        wpl = n < 2048 && two && !twice ? 2 : n <= 2048 || lines > 256 || twice ? 4 : 0;
         lpw = wpl == 2 ? 2 : 1;
+    } else if (n <= 2048) {
+        wpl = 2;
+        if (twice && (aligned || (n <= 1420 && units(2) < units(4)))) {
+            wpl = 4;
+            lpw = 2;
+        } else if (!aligned) {
+            if (3 * units(4) <= 5 * units(1)) lpw = 4;
+        } else if (lpw == 4 && (row != 0 || 3 * units(4) == 4 * units(1))) {
+            lpw = 2;
+        }
+        SweepCfg c;
+        if (!twice && choose_sweep_cfg_wpl(es, ndim, n, chi, wpl, lpw, &c, 1, asd::SWEEP_CELL_SLOTS) && c.lpw == lpw &&
+            resident_lines(es, ndim, n, c) >= std::min<int64_t>(6, units(lpw)))
+            body = asd::SWEEP_CELL_SLOTS;
     } else {
-        wpl = n <= 2048 ? 2 : 4;
+        wpl = 4;
     }
     if (keep) body = asd::SWEEP_FACE_SLOTS;
     for (; wpl > 0 && wpl <= 16; wpl *= 2)

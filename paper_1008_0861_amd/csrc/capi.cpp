@@ -163,17 +163,15 @@ size_t grid_workspace_bytes(const asd_desc* desc) { return plan_ws(desc).total; 
 bool set_default_cfg(asd_grid_s* g, int q) {
     const asd_desc& d = g->d;
     const int es = (int)g->es;
-    const bool chi = (d.flags & ASD_FLAG_PER_CELL_CHI) != 0, four = (d.flags & ASD_FLAG_FOUR_STEP) != 0;
-    auto shape = [&](int a, SweepCfg* c) {
-        return default_sweep_cfg(es, d.ndim, (int)d.n[a], g->N / d.n[a], chi, four, d.bc == ASD_BC_DIRICHLET, c);
+    const bool chi = (d.flags & ASD_FLAG_PER_CELL_CHI) != 0;
+    auto shape = [&](int a, bool twice, SweepCfg* c) {
+        return default_sweep_cfg(es, d.ndim, (int)d.n[a], g->N / d.n[a], chi, twice, d.bc == ASD_BC_DIRICHLET, c) &&
+               (!twice || twice_cfg(es, d.ndim, (int)d.n[a], *c, c));
     };
-    bool twice = four && d.chi_exp == 0.0;
+    bool twice = (d.flags & ASD_FLAG_FOUR_STEP) && d.chi_exp == 0.0;
     SweepCfg c;
-    for (int a = 0; a < d.ndim && twice; ++a)
-        twice = shape(a, &c) && twice_cfg(es, d.ndim, (int)d.n[a], c, &c);
-    if (!shape(q, &g->cfg[q])) return false;
-    if (twice) (void)twice_cfg(es, d.ndim, (int)d.n[q], g->cfg[q], &g->cfg[q]);
-    return true;
+    for (int a = 0; a < d.ndim && twice; ++a) twice = shape(a, true, &c);
+    return shape(q, twice, &g->cfg[q]);
 }
 
 bool default_line_cfg(asd_grid_s* g, int q, SweepCfg* out) {
