@@ -3,7 +3,8 @@ differentiable map (T0, chi) -> T_N.  The forward runs
 asd_adjoint_forward_states (the steps, storing a checkpoint every ckpt_every
 steps, or every state when there are at most two segments); the backward is
 the hand-written adjoint asd_adjoint_step_states, which recomputes each
-segment that was not stored from its checkpoint."""
+segment that was not stored from its checkpoint.  A forward that no gradient
+can follow stores the checkpoints alone."""
 import torch
 
 from . import binding
@@ -26,7 +27,7 @@ class SemiImplicitSteps(torch.autograd.Function):
             grid.set_field("chi", chi_c)
             T = T0.detach().clone()
             grid.set_field("T", T)
-            ws = grid.adjoint_forward(dt, nsteps, ckpt_every, states=True)
+            ws = grid.adjoint_forward(dt, nsteps, ckpt_every, states=any(ctx.needs_input_grad[:2]))
         cur.wait_stream(grid.stream)
         ctx.save_for_backward(chi_c)
         ctx.ws = ws  # the checkpoints (states at steps 0, k, 2k, ...), or all states
@@ -49,4 +50,6 @@ class SemiImplicitSteps(torch.autograd.Function):
 
 
 def semi_implicit_steps(T0, chi, grid, dt, nsteps, ckpt_every=10):
+    if not torch.is_grad_enabled():  # needs_input_grad is of the tensors, not of the mode
+        T0, chi = T0.detach(), chi.detach()
     return SemiImplicitSteps.apply(T0, chi, grid, dt, nsteps, ckpt_every)
