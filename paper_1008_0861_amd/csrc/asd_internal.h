@@ -168,11 +168,14 @@ inline int resident_lines(int es, int ndim, int n, const SweepCfg& c) {
 //   and four lines; 1200^2 45.6, 52.9 with two and two), but for rows off the half
 //   lines above 1420 cells (1500^2 68.8, 66.6; 1700^2 79.4, 70.4) or where that
 //   spares no CU a line (937 x 1403 37.3, 35.3).
-// - FP32 grids of fewer than 2^18 cells, and with T = 0 walls, keep face slots
-//   and one wave per line, with two staging and storing (256^2 7.9; cell slots 7.0,
-//   one staging wave 8.5, four lines per workgroup 9.1): the two bodies round
-//   differently, and a default keeps its results (the energies of both are as
-//   far from 64-bit arithmetic).
+// - FP32 with T = 0 walls keeps face slots: cell slots are faster (500^2 18.8,
+//   15.6), but the energy drifts more (against 64-bit arithmetic, 100 steps: 64^2
+//   1.4e-7, face slots 2e-8; 234^2 3.3e-8, 6e-9; only at 1024^2 less).
+// - FP32 grids of fewer than 2^18 cells keep face slots and one wave per line,
+//   with two staging and storing (256^2 7.9; cell slots 7.0, one staging wave 8.5,
+//   four lines per workgroup 9.1).  Both bodies are as far from 64-bit
+//   arithmetic there, but round differently (energies 1e-8 apart): the default
+//   keeps its results, the tuner takes cell slots.
 inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, bool twice, bool walls, SweepCfg* out) {
     const bool keep = es == 4 && ndim == 2 && (walls || (int64_t)n * lines < (1 << 18));
     auto units = [&](int64_t l) { return (lines + 256 * l - 1) / (256 * l) * l; };

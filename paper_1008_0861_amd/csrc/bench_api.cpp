@@ -223,9 +223,10 @@ extern "C" int asd_tune(asd_grid g, double dt, int32_t reps) {
     const bool chi = (g->d.flags & ASD_FLAG_PER_CELL_CHI) != 0;
     SweepCfg cur[3] = {g->cfg[0], g->cfg[1], g->cfg[2]};
     bool split[3] = {false, false, false};
-    // The two bodies round differently, which in FP32 shows in the energy of
-    // small grids, and there the timings are close enough for noise to decide:
-    // one body only, face slots with T = 0 walls (as default_sweep_cfg), else
+    // FP32, 2-D: one body only where the two round differently enough to show in
+    // the energies and noise could choose between them.  Face slots with T = 0
+    // walls, whose energies are the closer to 64-bit arithmetic (234^2, 100 steps:
+    // 6e-9, cell slots 3.3e-8); on other small grids, where both are as close,
     // cell slots (the faster ones, 256^2 6.8 us per step against 7.7).
     const bool f32_2d = g->es == 4 && g->d.ndim == 2, walls = g->d.bc == ASD_BC_DIRICHLET;
     const int last_body = f32_2d && walls ? SWEEP_FACE_SLOTS : SWEEP_CELL_SLOTS;

@@ -144,11 +144,12 @@ __global__ void __launch_bounds__(256) coef_t_kernel(CoefParams<T> C) {
 // The y and z sweeps' tiles need enough of them to fill the chip, more so with
 // chi(T), whose power takes longest.  us per one-step call that computes the
 // coefficients, cells / tiles: 256^2 FP32 15.1 / 16.1, 400^2 21.2 / 21.0, 64^3
-// with a per-cell chi 36.5 / 39.0, 80^3 67.7 / 54.8; chi(T), us per step: 256^2 17.6 / 24.9, 600^2 39.1 / 41.7, 64^3
-// 45.3 / 54.4, 80^3 81.2 / 78.8.  Short lines and chi(T), 300 x 300 x 4: 86 / 124,
-// x 12 FP32 157 / 173, FP64 235 / 211; rows shorter than half a tile, 8 x 400 x 400:
-// 159 / 315.  (A thread per cell of a row in chunks of 256, as the x sweep once
-// had, idles on short rows: 64 x 300 x 300 FP32 329, 294 by cells.)
+// with a per-cell chi 36.5 / 39.0, 80^3 67.7 / 54.8; chi(T), us per step: 256^2
+// 17.6 / 24.9, 600^2 39.1 / 41.7, 64^3 45.3 / 54.4, 80^3 81.2 / 78.8.  Short lines
+// and chi(T), 300 x 300 x 4: 86 / 124, x 12 FP32 157 / 173, FP64 235 / 211; rows
+// shorter than half a tile, 8 x 400 x 400: 159 / 315.  (A thread per cell of a row
+// in chunks of 256 idles on short rows in the x sweep: 64 x 300 x 300 FP32 329,
+// 294 by cells.)
 static bool coef_by_cells(int es, int ndim, int d, const int n[3], bool of_T) {
     const int64_t N = (int64_t)n[0] * n[1] * n[2];
     return d == 0 || N <= (of_T ? 1 << 19 : ndim == 3 ? 1 << 18 : 1 << 17) || n[0] < 16 || (of_T && n[d] <= 48 / es);

@@ -6,9 +6,10 @@
 namespace asd {
 
 // 2-D transpose: in [ny][nx] -> out [nx][ny].  A block takes a 64 x 64 tile
-// through LDS (a padded row: conflict-free both ways); rows of 64 elements
-// keep every access to memory whole cache lines, and a thread's sixteen
-// loads are all in flight before the first is used.
+// through LDS (a padded row: conflict-free both ways).  A wave loads and
+// stores 64 consecutive elements: whole cache lines where the rows of that
+// side start on them; elsewhere neighbouring tiles share each row's edge lines.
+// A thread's sixteen loads are all in flight before the first is used.
 template <typename T>
 __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int nx, int ny) {
     constexpr int W = 64, R = 16;
