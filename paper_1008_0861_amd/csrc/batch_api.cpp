@@ -480,10 +480,17 @@ static int batch_step_t(asd_batch b, int nsteps, int mode, double* energy) {
         if (!(b->dt[p] > 0.0)) return asd_fail(ASD_ENOTSET, "problem %d has not been set", p);
         int rc = check_fields(g, true);
         if (rc) return rc;
-        const bool was_valid = g->coef_valid && g->coef_dt == b->dt[p];
-        rc = prepare(g, b->dt[p]);
+        if (!(g->coef_valid && g->coef_dt == b->dt[p])) b->dirty = true;
+    }
+    // before the coefficients are enqueued, which its wait would take in (first
+    // call of 60 problems 1.59 ms, 1.43 in this order)
+    if (mode != 1) {
+        int rc = batch_tables<T>(b);
         if (rc) return rc;
-        if (!was_valid) b->dirty = true;
+    }
+    for (int p = 0; p < b->nprob; ++p) {
+        int rc = prepare(b->sub[p], b->dt[p]);
+        if (rc) return rc;
     }
     if (mode == 1) {
         for (int p = 0; p < b->nprob; ++p) {
@@ -494,8 +501,6 @@ static int batch_step_t(asd_batch b, int nsteps, int mode, double* energy) {
         }
         return ASD_OK;
     }
-    int rc = batch_tables<T>(b);
-    if (rc) return rc;
     // a captured call holds (2 + 1/ring) nsteps launches: calls longer than
     // the cap launch directly, as the single grids do
     if (b->use_graphs && b->st && nsteps >= 2 && nsteps <= kBatchGraphMaxSteps)
