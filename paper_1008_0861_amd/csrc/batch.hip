@@ -157,8 +157,12 @@ __global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
     }
 }
 
+// FP64 tiles of 8 cells with walls need 130 registers, two more than leave
+// room for two workgroups of 512 threads on a CU: held to 128 (60 problems with
+// T = 0 walls, FP64, face slots, us per step: 512 threads 124 against 161, 256
+// threads 119 against 124).
 template <typename T, int MMAX, int LIM, bool EXT, bool CELL>
-__global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads))
+__global__ void __launch_bounds__((BatchBounds<T, MMAX, CELL>::max_threads), (EXT && !CELL && sizeof(T) == 8 && MMAX == 8 ? 4 : 1))
     batch_grouped_kernel(const BatchProblem<T>* probs, const int* group_start, int nprob, int d, double* partials) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x;
