@@ -530,11 +530,6 @@ int check_dt(asd_grid g, double dt, bool explicit_scheme) {
     return ASD_OK;
 }
 
-// The whole multi-step call as a kernel sequence (used eagerly and under
-// graph capture).  Outputs: the initial state is reduced and folded first;
-// every step's last kernel writes per-block partials into the next ring
-// slot, and one fold launch turns a full ring (or the last steps) into the
-// outputs of each of those steps, off the sweeps' critical path.
 // Workgroups of one launch of sweep d in launch shape c.
 static int64_t sweep_num_blocks(asd_grid g, int d, const SweepCfg& c) {
     const SweepGeom G = sweep_geom(g->d.ndim, d);
@@ -583,6 +578,11 @@ int enqueue_direction(asd_grid g, const StepPlan& plan, int d, double dt, const 
     return rc ? rc : enqueue_permute_2d(g, spare, out, d == 0);
 }
 
+// The whole multi-step call as a kernel sequence (used eagerly and under
+// graph capture).  Outputs: the initial state is reduced and folded first;
+// every step's last kernel writes per-block partials into the next ring
+// slot, and one fold launch turns a full ring (or the last steps) into the
+// outputs of each of those steps, off the sweeps' critical path.
 int enqueue_si_loop(asd_grid g, double dt, int nsteps, const StepOut& outs) {
     const int nd = g->d.ndim;
     const StepPlan plan = step_plan(g);
