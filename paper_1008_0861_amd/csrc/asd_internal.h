@@ -137,24 +137,29 @@ inline int resident_lines(int es, int ndim, int n, const SweepCfg& c) {
 //   4 lines, 18.9 with 8), fewer where that keeps more CUs busy: l grows while
 //   it costs at most a third more (FP32 256^2 7.0 with 1 line, 7.4 with 4), on
 //   FP32 lines of more than 1024 cells less than that for the fourth (1536^2
-//   39.0 with 2 lines, 41.0 with 4; 1792^2 41.4, 38.4).
+//   39.0 with 2 lines, 41.0 with 4; 1792^2 41.4, 38.4).  FP64 lines of up to 512
+//   cells take pieces of 32 bytes (432 x 1649 26.5, 28.0; 500 x 777 20.8, 22.0).
 // - Rows that start on half lines of the cache (64 bytes) keep short pieces
-//   together: at most 2 lines (FP32 2000^2 49.1, 53.3 with 4; 1904^2 46.1, 48.2).
+//   together: at most 2 lines (FP32 2000^2 49.1, 53.3 with 4; 1904^2 46.1, 48.2),
+//   and so do rows one element short of that (x sweep of 1936 x 1935 23, 28).
 //   Rows that start anywhere need whole pieces, up to two thirds more load:
 //   FP32 1403^2 35.8 with 4 lines, 47.9 with 2; 1210^2 33.3, 38.1.
 // - FP32 body, above 1024 cells: cell slots while a CU holds six lines of them, or
 //   all that it gets (1392^2 28.4 with 2 lines, face slots 33.7; 1536^2, four
 //   lines, 49.6 and 39.1; 1344^2 with 4 lines per workgroup, four lines, 38.5 and
-//   33.8), on up to 1024 always (1024^2 16.6 against 19.1).
+//   33.8), unless its last lines then leave it a third empty (2000 x 1200, eight
+//   lines and six held, 39.9 and 36.2); on up to 1024 always (1024^2 16.6 against
+//   19.1).
 // - Waves per line: at most 8 cells per lane with cell slots up to 1024 cells, 16
 //   above and with face slots.
 // - FP64, up to 1024 cells: cell slots, on two waves from 7 of a lane's 8 cells up
 //   (1024^2 22.0, face slots 27.0; 960^2 26.3, 29.5; 768^2 30.0, 24.6) or with at
-//   most a line per CU (600 x 60 11.4, 11.8).
+//   most a line per CU (600 x 60 11.4, 11.8); on one wave while a CU holds all its
+//   lines (512^2 12.7; 500 x 3000, twelve lines and eight held, 55.6, face 53.2).
 // - FP64, 1025 to 2048: four waves and one line (1400^2 50.6, two waves and two
 //   lines 66.1), but two and two where rows start off the half lines (1403^2
-//   67.8, 83.2; 1100^2 52.1, 62.1) or every lane is nearly full and no CU loaded
-//   more (1920^2 78.0, 81.5).  Longer lines: four waves (3000 x 300 40.5, eight
+//   67.8, 83.2; 1100^2 52.1, 62.1) or every lane is nearly full, a CU has more than
+//   two lines and none more for it (1920^2 78.0, 81.5; 1999 x 512 29.9, 28.2).  Longer lines: four waves (3000 x 300 40.5, eight
 //   waves 47.3), eight where there is at most a line per CU (3000 x 100 25.0, 23.9), but for
 //   the two-solve launches (256 x 4096 33.8, eight waves 40.5).
 // - 3-D: FP32 cell slots and 4 lines (256^3 261, face slots 299; 200^3 142,
@@ -180,8 +185,13 @@ inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, 
     const bool keep = es == 4 && ndim == 2 && (walls || (int64_t)n * lines < (1 << 18));
     auto units = [&](int64_t l) { return (lines + 256 * l - 1) / (256 * l) * l; };
     int lpw = 1, wpl = 0, io = 1, body = asd::SWEEP_FACE_SLOTS;
-    for (int l = 2; l <= 16 / es; l *= 2)
+    for (int l = 2; l <= (es == 4 || (ndim == 2 && n <= 512) ? 4 : 2); l *= 2)
         if (3 * units(l) <= 4 * units(1)) lpw = l;
+    // lines of cell slots that a CU holds in this shape
+    auto cell_lines = [&](int w, int l) {
+        SweepCfg c;
+        return choose_sweep_cfg_wpl(es, ndim, n, chi, w, l, &c, 1, asd::SWEEP_CELL_SLOTS) && c.lpw == l ? resident_lines(es, ndim, n, c) : 0;
+    };
     const int64_t row = lines * es % 128;  // of the transposed output
     const bool aligned = row % 64 == 0;
     if (ndim == 3) {
@@ -196,9 +206,9 @@ inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, 
         lpw = std::max(lpw, io);
     } else if (n <= 1024) {
         wpl = n <= 512 ? 1 : 2;
-        if (es == 4 || n <= 512 || n >= 7 * 128 || lines <= 256) body = asd::SWEEP_CELL_SLOTS;
+        if (es == 4 || n >= 7 * 128 || lines <= 256 || (n <= 512 && cell_lines(wpl, lpw) >= units(lpw))) body = asd::SWEEP_CELL_SLOTS;
     } else if (es == 8) {
-        const bool two = aligned ? n > 14 * 128 && units(2) == units(1) : lpw == 2;
+        const bool two = aligned ? n > 14 * 128 && lines > 512 && units(2) == units(1) : lpw == 2;
         wpl = n < 2048 && two && !twice ? 2 : n <= 2048 || lines > 256 || twice ? 4 : 0;
         lpw = wpl == 2 ? 2 : 1;
     } else if (n <= 2048) {
@@ -206,14 +216,13 @@ inline bool default_sweep_cfg(int es, int ndim, int n, int64_t lines, bool chi, 
         if (twice && (aligned || (n <= 1420 && units(2) < units(4)))) {
             wpl = 4;
             lpw = 2;
-        } else if (!aligned) {
+        } else if (!aligned && (row % 64 != 60 || twice)) {
             if (3 * units(4) <= 5 * units(1)) lpw = 4;
         } else if (lpw == 4 && (row != 0 || 3 * units(4) == 4 * units(1))) {
             lpw = 2;
         }
-        SweepCfg c;
-        if (!twice && choose_sweep_cfg_wpl(es, ndim, n, chi, wpl, lpw, &c, 1, asd::SWEEP_CELL_SLOTS) && c.lpw == lpw &&
-            resident_lines(es, ndim, n, c) >= std::min<int64_t>(6, units(lpw)))
+        const int64_t u = units(lpw), held = twice ? 0 : cell_lines(wpl, lpw);
+        if (held >= std::min<int64_t>(6, u) && (held >= u || 3 * ((u + held - 1) / held) * held <= 4 * u))
             body = asd::SWEEP_CELL_SLOTS;
     } else {
         wpl = 4;

@@ -55,7 +55,13 @@ def sweep_shape(shape, dtype, axis=0, **kw):
     ((1792, 1792), F32, (FACE, 2, 4)),
     ((2000, 2000), F32, (FACE, 2, 2)),   # rows on half lines
     ((2048, 2048), F32, (FACE, 2, 4)),
+    ((2000, 1200), F32, (FACE, 2, 2)),   # eight lines per CU, six held with cell slots
+    ((2320, 1280), F32, (CELL, 2, 2)),   # ten lines: the second round is nearly full
+    ((1935, 1936), F32, (FACE, 2, 2)),   # rows one element short of a half line
     ((512, 512), F64, (CELL, 1, 2)),
+    ((1649, 432), F64, (CELL, 1, 4)),
+    ((3000, 500), F64, (FACE, 1, 4)),
+    ((512, 1999), F64, (FACE, 4, 1)),
     ((768, 768), F64, (FACE, 2, 2)),
     ((60, 600), F64, (CELL, 2, 1)),
     ((896, 896), F64, (CELL, 2, 2)),
